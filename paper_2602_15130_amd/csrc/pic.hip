@@ -230,6 +230,8 @@ struct pic_ctx {
   bool mom_ready = false;         // cell moments of the current positions deposited by the sort
   bool heavy = false;           // collision calls by k_collide_heavy (many pairs per outcome)
   int heavy_bits = 0;           // its fixed-point scale
+  int heavy_lds_n = 0;          // cells up to this size accumulate in its LDS
+  int heavy_split = 1;          // its workgroups per cell
   double* angbuf = nullptr;     // scattering-angle records and their sort scratch
   int64_t angcap = 0;
   LowArgs low{};
@@ -552,8 +554,19 @@ int collide(pic_ctx* c, int call, int64_t step, double* D, long long* pairlog, i
   StageTimer tm(c, PIC_STAGE_COLLIDE);
   if (c->heavy) {
     // workgroup per cell; the few cells beyond its capacity run one thread each
-    k_collide_heavy<<<K.nn, 64 * kHeavyWaves, kHeavyLdsBytes, c->stream>>>(
-        K, call, step, c->v[c->cur], c->cstart, D, c->heavy_bits, pairlog, cap, c->cnt, c->flags);
+    // (the sort's index arrays and the FP64 scratch are idle here)
+    const int hsig = K.sigma_model == 0 ? kSigPoly : (K.omega == 1.0 ? kSigMaxwell : kSigHS);
+    const bool full = K.anglog != nullptr || pairlog != nullptr || K.chi_model != PIC_CHI_ISO ||
+                      K.coding_error != 0;
+    auto hfn = hsig == kSigHS        ? (full ? k_collide_heavy<kSigHS, true> : k_collide_heavy<kSigHS, false>)
+               : hsig == kSigMaxwell ? (full ? k_collide_heavy<kSigMaxwell, true> : k_collide_heavy<kSigMaxwell, false>)
+                                     : (full ? k_collide_heavy<kSigPoly, true> : k_collide_heavy<kSigPoly, false>);
+    if (c->heavy_split > 1) TRY(fill<double>(c, D, 0.0, 3 * K.np));
+    hfn<<<dim3(K.nn, c->heavy_split), kHeavyThreads, c->heavy_lds_n * 3 * sizeof(long long), c->stream>>>(
+        K, call, step, c->v[c->cur], c->cstart, D, c->U, c->V0G, (unsigned*)c->tidx, c->heavy_lds_n,
+        c->heavy_bits, pairlog, cap, c->cnt, c->flags);
+    if (c->heavy_split > 1)
+      k_heavy_finish<<<grid_for(3 * K.np), kBlock, 0, c->stream>>>(K, D, c->heavy_bits);
     LAUNCH_CHECK(c, "collide (heavy)");
     // (the sort's index arrays are idle here: marks and touched lists)
     const int sig = K.sigma_model == 0 ? kSigPoly : (K.omega == 1.0 ? kSigMaxwell : kSigHS);
@@ -1056,12 +1069,15 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     const double pairs = nbar * (nbar - 1.0) * c->K.pmax / 2.0;
     bool heavy = precision == PIC_FP64 && c->K.collisions && (double)c->K.navg * pairs >= 64.0;
     if (const char* h = std::getenv("PIC_HEAVY")) heavy = precision == PIC_FP64 && h[0] == '1';
-    if (heavy && hipFuncSetAttribute((const void*)k_collide_heavy,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)kHeavyLdsBytes) != hipSuccess) {
-      (void)hipGetLastError();
-      heavy = false;
-    }
+    // Accumulators in LDS for cells up to about three times the mean (the
+    // paper's density peaks at 2.6 times it); 24 B a particle, so at most
+    // kHeavyMaxLdsN particles leave the CU room for a few workgroups.
+    c->heavy_lds_n = (int)std::min<double>(kHeavyMaxLdsN, 64.0 * std::ceil(std::max(3.0 * nbar, 1.0) / 64.0));
+    // Workgroups per cell: the mean cell's 64-pair batches, kHeavyBatches to a
+    // wave (the densest cells have three times the mean's pairs: with one
+    // workgroup each the last of them run alone).
+    c->heavy_split = (int)std::max(1.0, std::min(64.0, std::ceil((double)c->K.navg * (pairs + 1.0) /
+                                                                 (64.0 * kHeavyWaves * kHeavyBatches))));
     if (members > 1) {  // ensembles run the fused passes, whose kernels take members
       heavy = false;
       c->fused = true;

@@ -856,11 +856,13 @@ __device__ inline void record_angles(const R up[3], const R uq[3], R g, double* 
 
 __device__ inline uint64_t redraw_word(const SimConst& K, int cell, int64_t step, int call, int k,
                                        int64_t m, const U64x4& wb, int r) {
-  if (r < 3) return wb.w[1 + r];
+  // (words picked by selects: an index would put the block into scratch memory)
+  if (r < 3) return r == 0 ? wb.w[1] : (r == 1 ? wb.w[2] : wb.w[3]);
   int64_t j = (r - 3) / 4;
   U64x4 b = stream_block(K, (uint64_t)cell, (uint64_t)step, kTagRedraw, (uint64_t)call,
                          (uint64_t)k, ((uint64_t)m << 16) | (uint64_t)j);
-  return b.w[(r - 3) % 4];
+  const int i = (r - 3) % 4;
+  return i < 2 ? (i == 0 ? b.w[0] : b.w[1]) : (i == 2 ? b.w[2] : b.w[3]);
 }
 
 // Candidate partner q != p: Algorithm 1 redraws q while it equals p.
@@ -927,15 +929,17 @@ __device__ inline void post_collision(const SimConst& K, const R up[3], const R 
   }
 }
 
-// Capacity of the workgroup-per-cell collision kernel (k_collide_heavy):
-// particles per cell and candidate pairs per outcome.  A cell that could
-// exceed either (N_pairs = floor(n (n - 1) P_max / 2 + U) < n (n - 1) P_max / 2 + 1)
-// is a "big" cell; in the collision-heavy mode it runs in k_collide_big instead.
-constexpr int kHeavyMaxN = 2048;
+// Capacity of the workgroup-per-cell collision kernel (k_collide_heavy): an
+// outcome's pairs fit its LDS (kHeavyMaxPairs) or the cell's scratch, which
+// holds one pair per particle of the cell.  A cell that could exceed both
+// (N_pairs = floor(n (n - 1) P_max / 2 + U) <= n (n - 1) P_max / 2 + 1) is a
+// "big" cell; in the collision-heavy mode it runs in k_collide_big instead.
+constexpr int kHeavyMaxN = 0xfffe;  // (two 16-bit slots to a word)
 constexpr int kHeavyMaxPairs = 192;
 __device__ inline bool heavy_big_cell(const SimConst& K, int n) {
+  const double most = (double)n * (double)(n - 1) * K.pmax / 2.0 + 1.0;
   return n > kHeavyMaxN ||
-         (double)n * (double)(n - 1) * K.pmax / 2.0 + 1.0 >= (double)(kHeavyMaxPairs + 1);
+         (most >= (double)(kHeavyMaxPairs + 1) && !(most < (double)n && most < (double)kMaxPairsPerOutcome));
 }
 
 __global__ void __launch_bounds__(kBlock) k_collide_f64(SimConst K, int call, int64_t step,
