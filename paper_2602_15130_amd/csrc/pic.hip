@@ -18,6 +18,7 @@
 #include "pic_mixed.hpp"
 #include "pic_cg_brick.hpp"
 #include "pic_lowmode.hpp"
+#include "pic_direct.hpp"
 #include "pic_angles.hpp"
 #include "pic_collide_heavy.hpp"
 #include "pic_order.hpp"
@@ -38,7 +39,7 @@ enum Arr {
   A_KEY, A_SLOT, A_TIDX, A_TKEY, A_D, A_U, A_V0G,
   A_COUNT, A_CSTART, A_BSUM, A_TILE, A_MOM, A_RHO, A_B, A_PHI, A_E, A_E32, A_CGV, A_LOW,
   A_PART_A, A_PART_B, A_EPART, A_NPART, A_NORMS, A_BAR, A_RESULT, A_FLAGS, A_CNT, A_CGIT, A_CGRR,
-  A_DEFER, A_STEPC, A_MIXC,
+  A_DEFER, A_STEPC, A_MIXC, A_DIRECT, A_CHECK, A_MEAN,
   A_NARR
 };
 
@@ -93,6 +94,9 @@ Layout make_layout(const pic_discretization* d, int precision) {
   b[A_DEFER] = ((np + kTileB - 1) / kTileB + 1) * 4;  // tiles the lean pass leaves to the general one
   b[A_STEPC] = 8;                   // completed steps, for captured steps
   b[A_MIXC] = sizeof(MixConst);     // the mixed pass's constants of a captured step
+  b[A_DIRECT] = direct_table_doubles(d->ncell) * 8;  // the direct solve's tables
+  b[A_CHECK] = 2 * std::min<int64_t>(nblk_n, kCheckBlocks) * 8;
+  b[A_MEAN] = 8;
   int64_t t = 0;
   for (int i = 0; i < A_NARR; ++i) {
     L.off[i] = t;
@@ -225,6 +229,8 @@ struct pic_ctx {
   int cg_nbr[3] = {0, 0, 0};    // bricks per axis
   size_t cg_lds = 0;            // padded brick, bytes of LDS
   int low_k = 0;                // Fourier modes per axis solved exactly before the CG
+  bool direct = false;          // all of them (pic_direct.hpp); the CG then only finishes
+  size_t direct_lds = 0;        // LDS of the one-launch direct solve, 0 = one launch per transform
   size_t low_lds[3] = {0, 0, 0};  // dynamic LDS of the three pre-solve passes
   bool count_zero = false;        // cell counts known to be zero (left so by the scan)
   bool mom_ready = false;         // cell moments of the current positions deposited by the sort
@@ -235,6 +241,7 @@ struct pic_ctx {
   double* angbuf = nullptr;     // scattering-angle records and their sort scratch
   int64_t angcap = 0;
   LowArgs low{};
+  DirectArgs dir{};
   bool ready = false;
   int64_t step = 0;
   int cur = 0;
@@ -266,7 +273,7 @@ struct pic_ctx {
   void* mom{};
   double *rho{}, *b{}, *phi{}, *E{}, *cgv{}, *lowbuf{}, *partA{}, *partB{};
   float* E32{};
-  double *epart{}, *npart{}, *norms{}, *cgrr{}, *result{};
+  double *epart{}, *npart{}, *norms{}, *cgrr{}, *result{}, *check{};
   unsigned* bar{};
   int *flags{}, *cgit{};
   unsigned long long* cnt{};
@@ -451,6 +458,37 @@ int sort_particles(pic_ctx* c) {
   return PIC_OK;
 }
 
+template <int MODE>
+void direct_axis(pic_ctx* c) {
+  const SimConst& K = c->K;
+  const int64_t nx = K.nc[0], ny = K.nc[1], nz = K.nc[2];
+  constexpr bool X = MODE == 0 || MODE == 5, Y = MODE == 1 || MODE == 4;
+  const int64_t M = X ? ny * nz : (Y ? ny : nz), N = X || Y ? nx : nx * ny, batches = Y ? nz : 1;
+  auto tiles = [](int64_t n, int t) { return (n + t - 1) / t; };
+  if (tiles(M, 64) * tiles(N, 64) * batches * c->members >= 256)
+    k_direct_axis<MODE, 64><<<G(c, (unsigned)(tiles(M, 64) * batches), (unsigned)tiles(N, 64)), 256, 0,
+                              c->stream>>>(K, c->dir);
+  else
+    k_direct_axis<MODE, 32><<<G(c, (unsigned)(tiles(M, 32) * batches), (unsigned)tiles(N, 32)), 256, 0,
+                              c->stream>>>(K, c->dir);
+}
+
+// x corrected by the full-spectrum solve of its residual.
+int direct_solve(pic_ctx* c) {
+  if (c->direct_lds > 0) {
+    k_direct_small<<<G(c, 1), kDirectSmallThreads, c->direct_lds, c->stream>>>(c->K, c->dir);
+  } else {
+    direct_axis<0>(c);
+    direct_axis<1>(c);
+    direct_axis<2>(c);
+    direct_axis<3>(c);
+    direct_axis<4>(c);
+    direct_axis<5>(c);
+  }
+  LAUNCH_CHECK(c, "direct solve");
+  return PIC_OK;
+}
+
 // deposit -> RHS (eq. poisson_mms, mean removed) -> CG (warm start) -> E = -grad phi
 int field_solve(pic_ctx* c, double t) {
   const SimConst& K = c->K;
@@ -468,7 +506,8 @@ int field_solve(pic_ctx* c, double t) {
         k_deposit_moments_f64<<<nbn, kBlock, 0, c->stream>>>(K, c->x[c->cur], c->cstart,
                                                              (double*)c->mom);
       k_node_rhs<double><<<G(c, nbn), kBlock, 0, c->stream>>>(K, (const double*)c->mom, t, c->rho, c->b,
-                                                        c->partA, c->capturing ? c->stepc : nullptr);
+                                                        c->partA, c->phi, c->direct ? c->dir.w : nullptr,
+                                                        c->capturing ? c->stepc : nullptr);
     } else {
       if (!have_mom && c->fused)
         k_deposit_tiles_mixed<<<G(c, ntiles), kTileThreads, 0, c->stream>>>(K, c->off[c->cur], c->cstart,
@@ -477,16 +516,30 @@ int field_solve(pic_ctx* c, double t) {
         k_deposit_moments_mixed<<<nbn, kBlock, 0, c->stream>>>(K, c->off[c->cur], c->cstart,
                                                                (float*)c->mom);
       k_node_rhs_mixed<<<G(c, nbn), kBlock, 0, c->stream>>>(K, (const float*)c->mom, t, c->rho, c->b,
-                                                      c->partA, c->capturing ? c->stepc : nullptr);
+                                                      c->partA, c->phi, c->direct ? c->dir.w : nullptr,
+                                                      c->capturing ? c->stepc : nullptr);
     }
-    // also zeroes the solver's arrival flags and release word
-    k_sub_mean<<<G(c, nbn), kBlock, 0, c->stream>>>(K, c->b, c->partA, nbn, c->bar,
+    // also zeroes the solver's arrival flags and release word (after a direct
+    // solve its check does both)
+    if (!c->direct) k_sub_mean<<<G(c, nbn), kBlock, 0, c->stream>>>(K, c->b, c->partA, nbn, c->bar,
                                               (c->cg_grid + 1) * kFlagStride);
     LAUNCH_CHECK(c, "rhs");
   }
+  const int ncheck = std::min(nbn, kCheckBlocks);
+  if (c->direct) {
+    {
+      StageTimer tm(c, PIC_STAGE_CG);
+      TRY(direct_solve(c));
+    }
+    StageTimer tm(c, PIC_STAGE_GRADIENT);
+    k_direct_check<<<G(c, ncheck), kBlock, 0, c->stream>>>(K, c->b, c->phi, c->dir.mean, c->check,
+                                                           c->E, c->E32, c->bar,
+                                                           (c->cg_grid + 1) * kFlagStride);
+    LAUNCH_CHECK(c, "direct solve");
+  }
   // the Poisson solve (low-mode pre-solve and CG) is timed as one stage
   StageTimer tm_solve(c, PIC_STAGE_CG);
-  if (c->low_k > 0) {  // exact solve of the low Fourier modes of the residual
+  if (!c->direct && c->low_k > 0) {  // exact solve of the low Fourier modes of the residual
     const LowArgs& L = c->low;
     const int planes = L.slabs * K.nc[2];
     k_low_project<<<G(c, planes), kLowThreads, c->low_lds[0], c->stream>>>(K, L, c->b, c->phi);
@@ -519,6 +572,13 @@ int field_solve(pic_ctx* c, double t) {
     a.bdim[d] = c->cg_bd[d];
     a.nbr[d] = c->cg_nbr[d];
   }
+  a.check = c->check;
+  a.ncheck = c->direct ? ncheck : 0;
+  a.E = c->E;
+  a.E32 = c->E32;
+  // After a direct solve the launch seldom has work, so members whose solvers
+  // do not fit together share one launch all the same, one after another.
+  a.members = c->direct && !c->cg_members_together ? c->members : 1;
   SimConst Kc = K;
   void* args[] = {&Kc, &a};
   // The solver's workgroups wait for each other, so they must be co-resident:
@@ -536,6 +596,8 @@ int field_solve(pic_ctx* c, double t) {
     // every member's solver in one co-resident grid (members along z; each
     // member's bricks synchronise only among themselves)
     HIP_TRY(c, launch(G(c, c->cg_grid)));
+  } else if (c->direct) {
+    HIP_TRY(c, launch(dim3(c->cg_grid)));
   } else {
     for (int m = 0; m < c->members; ++m) {
       Kc.member0 = m;
@@ -543,6 +605,7 @@ int field_solve(pic_ctx* c, double t) {
     }
   }
   tm_solve.stop();
+  if (c->direct) return PIC_OK;  // (its check and the CG leave E)
   StageTimer tm(c, PIC_STAGE_GRADIENT);
   k_gradient<<<G(c, nbn), kBlock, 0, c->stream>>>(K, c->phi, c->E, c->E32);
   LAUNCH_CHECK(c, "gradient");
@@ -1155,6 +1218,7 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
   c->stepc = carve<long long>(c, A_STEPC);  // member 0's: one counter for all members
   c->mixc = carve<MixConst>(c, A_MIXC);
   c->K.stepc = c->stepc;
+  c->check = carve<double>(c, A_CHECK);
 
   // Cooperative grid for the Poisson solver: one block per CU at most, never
   // more than the node count needs, and never more than can be co-resident.
@@ -1284,6 +1348,40 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     }
   }
 
+  // The direct solve takes the place of the low-mode pre-solve unless the
+  // caller asked for a number of modes, or allows fewer CG iterations than the
+  // pre-solved CG may need (a call that is refused for that stays refused:
+  // 4 n covers it, 29 iterations at 128^3), or wants the residual below 1e-15 of
+  // the right-hand side, where rounding decides whether any solver gets there.
+  {
+    const int* nc = c->K.nc;
+    const int nmax = std::max({nc[0], nc[1], nc[2]});
+    c->direct = !std::getenv("PIC_CG_LOWMODES") && c->cg_max_iter >= 4 * nmax && c->cg_tol >= 1e-15;
+    DirectArgs& D = c->dir;
+    double* p = carve<double>(c, A_DIRECT);
+    for (int d = 0; d < 3; ++d) {
+      D.f[d] = p;
+      D.t[d] = p + (int64_t)nc[d] * nc[d];
+      p += 2 * (int64_t)nc[d] * nc[d];
+    }
+    D.lam = p;
+    D.nmax = nmax;
+    D.u = c->cgv;  // (the CG's vectors are idle until it starts)
+    D.w = c->cgv + (int64_t)c->K.nn;
+    D.x = c->phi;
+    D.part = c->partA;
+    D.nparts = grid_for(c->K.nn);
+    D.mean = carve<double>(c, A_MEAN);
+    int lds_cap = 65536;
+    (void)hipDeviceGetAttribute(&lds_cap, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    const size_t need = direct_small_lds(nc);
+    if (c->direct && need + 512 <= (size_t)lds_cap &&
+        hipFuncSetAttribute((const void*)k_direct_small, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)need) == hipSuccess)
+      c->direct_lds = need;
+    (void)hipGetLastError();
+  }
+
   auto init = [&]() -> int {
     const SimConst& K = c->K;
     TRY(fill<int>(c, c->flags, 0, kFlagCount));
@@ -1292,7 +1390,11 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     c->count_zero = false;
     TRY(zero_counts(c));
     TRY(fill<double>(c, c->phi, 0.0, K.nn));
-    if (c->low_k > 0) {
+    if (c->direct) {
+      const int64_t n = direct_table_doubles(K.nc);
+      k_direct_tables<<<G(c, grid_for(n)), kBlock, 0, c->stream>>>(K, (double*)c->dir.f[0], c->dir.nmax);
+      LAUNCH_CHECK(c, "direct-solve tables");
+    } else if (c->low_k > 0) {
       k_low_tables<<<G(c, grid_for((int64_t)3 * kLowMaxM * c->low.nmax)), kBlock, 0, c->stream>>>(
           K, c->low, (double*)c->low.tab, (double*)c->low.mu);
       LAUNCH_CHECK(c, "low-mode tables");

@@ -147,10 +147,8 @@ inline size_t brick_lds_bytes(const int bd[3]) {
 // lk = 0..Q-1, so its node q sits at padded index pl0 + q pxy and mesh node
 // gn0 + q nx ny (a brick never wraps inside).
 template <int Q, int NT>
-__global__ void __launch_bounds__(NT) k_cg_brick(SimConst K, CgArgs a) {
-  a = member_view(K, a);
-  extern __shared__ double R[];
-  __shared__ double sh[3 * (NT / 64)];
+__device__ __attribute__((always_inline)) inline void cg_brick_solve(const SimConst& K, const CgArgs& a,
+                                                                     double* R, double* sh) {
   const int bd[3] = {a.bdim[0], a.bdim[1], Q};
   int foff[7];
   brick_face_offsets(bd, foff);
@@ -322,6 +320,18 @@ __global__ void __launch_bounds__(NT) k_cg_brick(SimConst K, CgArgs a) {
   if (blockIdx.x == 0 && tid == 0) {
     *a.iters_out = it;
     *a.relres_out = bnorm == 0.0 ? 0.0 : sqrt(gamma) / bnorm;
+  }
+  cg_rebuild_field<NT>(K, a, ++gen, sh);
+}
+
+template <int Q, int NT>
+__global__ void __launch_bounds__(NT) k_cg_brick(SimConst K, CgArgs a0) {
+  extern __shared__ double R[];
+  __shared__ double sh[3 * (NT / 64)];
+  for (int m = 0; m < a0.members; ++m, ++K.member0) {
+    const CgArgs a = member_view(K, a0);
+    if (!direct_converged<NT>(a, sh)) cg_brick_solve<Q, NT>(K, a, R, sh);
+    __syncthreads();  // before the next member's solve reuses the LDS
   }
 }
 

@@ -483,13 +483,21 @@ __device__ inline double rhs_manufactured(const SimConst& K, int i, int j, int k
   return v;
 }
 
+// The residual of the warm start for the direct solve, r = -b - A x (b with its
+// mean, which only the constant mode sees), where the right-hand side is formed.
+__device__ inline void warm_residual(const SimConst& K, int n, int i, int j, int k, double bv,
+                                     const double* x, double* r);
+
 // Node charge and the right-hand side of eq. poisson_mms; block partial sums
-// of b for the mean removal.
+// of b for the mean removal.  resid: also the residual at x (direct solve), or null.
 template <class MomT>
 __global__ void __launch_bounds__(kBlock) k_node_rhs(SimConst K, const MomT* mom, double t,
                                                      double* rho, double* b, double* part,
+                                                     const double* x, double* resid,
                                                      const long long* tstep) {
   if (tstep) t = ((double)*tstep + 1.0) * K.dt;  // a captured step: the end of step *tstep
+  x = mem(K, x);
+  resid = mem(K, resid);
   mom = mem(K, mom);
   rho = mem(K, rho);
   b = mem(K, b);
@@ -513,6 +521,7 @@ __global__ void __launch_bounds__(kBlock) k_node_rhs(SimConst K, const MomT* mom
     bv = rhs_manufactured(K, i, j, k, t);
     if (K.p2f != 0.0) bv -= r / K.eps0;
     b[n] = bv;
+    if (resid) warm_residual(K, n, i, j, k, bv, x, resid);
   }
   double tot = block_sum(bv, sh);
   if (threadIdx.x == 0) part[blockIdx.x] = tot;
@@ -532,6 +541,23 @@ __global__ void __launch_bounds__(kBlock) k_sub_mean(SimConst K, double* b, cons
   double mean = block_sum(acc, sh) / (double)K.nn;
   int n = blockIdx.x * kBlock + threadIdx.x;
   if (n < K.nn) b[n] -= mean;
+}
+
+// E = -grad phi at node n = (i, j, k), central differences; optional FP32 copy
+// for the mixed form.
+__device__ inline void node_field(const SimConst& K, const double* phi, int n, int i, int j, int k,
+                                  double* E, float* E32) {
+  double ex = -(phi[lin(K, i + 1, j, k)] - phi[lin(K, i - 1, j, k)]) / (2.0 * K.h[0]);
+  double ey = -(phi[lin(K, i, j + 1, k)] - phi[lin(K, i, j - 1, k)]) / (2.0 * K.h[1]);
+  double ez = -(phi[lin(K, i, j, k + 1)] - phi[lin(K, i, j, k - 1)]) / (2.0 * K.h[2]);
+  E[n] = ex;
+  E[K.nn + n] = ey;
+  E[2 * K.nn + n] = ez;
+  if (E32) {
+    E32[3 * n] = (float)ex;
+    E32[3 * n + 1] = (float)ey;
+    E32[3 * n + 2] = (float)ez;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -574,6 +600,14 @@ struct CgArgs {
   double* pub;        // brick solver: published faces, [bricks][2][3][nh]
   int bdim[3];        // brick solver: nodes per brick along each axis
   int nbr[3];         // brick solver: bricks along each axis
+  // After a direct solve (ncheck > 0): its check, [2][ncheck] block sums of r^2
+  // and b^2, with which the kernel leaves at once when x already meets the
+  // tolerance, else runs and rebuilds E (and its FP32 copy) at the end.
+  const double* check;
+  int ncheck;
+  double* E;
+  float* E32;
+  int members;        // members solved by the launch one after another (the grid serves one)
 };
 
 __device__ inline bool spin_until(const unsigned* addr, unsigned want, int* flags) {
@@ -609,6 +643,9 @@ __device__ inline CgArgs member_view(const SimConst& K, CgArgs a) {
   a.iters_out = mem(K, a.iters_out);
   a.relres_out = mem(K, a.relres_out);
   a.pub = mem(K, a.pub);
+  a.check = mem(K, a.check);
+  a.E = mem(K, a.E);
+  a.E32 = mem(K, a.E32);
   return a;
 }
 
@@ -713,9 +750,45 @@ __device__ inline double neg_lap(const SimConst& K, int i, int j, int k, const F
   return -(lx * K.ih2[0] + ly * K.ih2[1] + lz * K.ih2[2]);
 }
 
-__global__ void __launch_bounds__(kBlock) k_cg(SimConst K, CgArgs a) {
-  a = member_view(K, a);
-  __shared__ double sh[3 * kWaves];
+__device__ inline void warm_residual(const SimConst& K, int n, int i, int j, int k, double bv,
+                                     const double* x, double* r) {
+  r[n] = -bv - neg_lap(K, i, j, k, [&](int m) { return x[m]; });
+}
+
+// Whether the direct solve before this launch already met the tolerance (the
+// same sums in the same order in every workgroup).
+template <int NT>
+__device__ inline bool direct_converged(const CgArgs& a, double* sh) {
+  if (a.ncheck <= 0) return false;
+  double v[kMaxRed] = {0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < a.ncheck; i += NT) {
+    v[0] += a.check[i];
+    v[1] += a.check[a.ncheck + i];
+  }
+  block_sum3_t<NT>(v, 2, sh);
+  const double bnorm = sqrt(v[1]);
+  if (!(bnorm > 0.0 && sqrt(v[0]) <= a.tol * bnorm)) return false;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *a.iters_out = 0;
+    *a.relres_out = sqrt(v[0]) / bnorm;
+  }
+  return true;
+}
+
+// E from the potential that the CG left, after a direct solve that fell short.
+template <int NT>
+__device__ inline void cg_rebuild_field(const SimConst& K, const CgArgs& a, unsigned gen, double* sh) {
+  if (a.ncheck <= 0) return;
+  double z[kMaxRed] = {0.0, 0.0, 0.0};
+  if (!grid_sum_t<NT>(a, z, 1, gen, sh)) return;  // every workgroup's part of x is visible
+  for (int n = blockIdx.x * NT + threadIdx.x; n < K.nn; n += gridDim.x * NT) {
+    int i, j, k;
+    node_coords(K, n, i, j, k);
+    node_field(K, a.x, n, i, j, k, a.E, a.E32);
+  }
+}
+
+__device__ inline void cg_solve(const SimConst& K, const CgArgs& a, double* sh) {
   const int gsize = gridDim.x * kBlock;
   const int g0 = blockIdx.x * kBlock + threadIdx.x;
   unsigned gen = 0;
@@ -802,9 +875,17 @@ __global__ void __launch_bounds__(kBlock) k_cg(SimConst K, CgArgs a) {
     *a.iters_out = it;
     *a.relres_out = bnorm == 0.0 ? 0.0 : sqrt(gamma) / bnorm;
   }
+  cg_rebuild_field<kBlock>(K, a, ++gen, sh);
 }
 
-// E = -grad phi, central differences; optional FP32 copy for the mixed form.
+__global__ void __launch_bounds__(kBlock) k_cg(SimConst K, CgArgs a0) {
+  __shared__ double sh[3 * kWaves];
+  for (int m = 0; m < a0.members; ++m, ++K.member0) {
+    const CgArgs a = member_view(K, a0);
+    if (!direct_converged<kBlock>(a, sh)) cg_solve(K, a, sh);
+  }
+}
+
 __global__ void __launch_bounds__(kBlock) k_gradient(SimConst K, const double* phi, double* E,
                                                      float* E32) {
   phi = mem(K, phi);
@@ -814,17 +895,7 @@ __global__ void __launch_bounds__(kBlock) k_gradient(SimConst K, const double* p
   if (n >= K.nn) return;
   int i, j, k;
   node_coords(K, n, i, j, k);
-  double ex = -(phi[lin(K, i + 1, j, k)] - phi[lin(K, i - 1, j, k)]) / (2.0 * K.h[0]);
-  double ey = -(phi[lin(K, i, j + 1, k)] - phi[lin(K, i, j - 1, k)]) / (2.0 * K.h[1]);
-  double ez = -(phi[lin(K, i, j, k + 1)] - phi[lin(K, i, j, k - 1)]) / (2.0 * K.h[2]);
-  E[n] = ex;
-  E[K.nn + n] = ey;
-  E[2 * K.nn + n] = ez;
-  if (E32) {
-    E32[3 * n] = (float)ex;
-    E32[3 * n + 1] = (float)ey;
-    E32[3 * n + 2] = (float)ez;
-  }
+  node_field(K, phi, n, i, j, k, E, E32);
 }
 
 // ---------------------------------------------------------------------------

@@ -195,8 +195,11 @@ __global__ void __launch_bounds__(kTileThreads) k_deposit_tiles_mixed(SimConst K
 // right-hand side of eq. poisson_mms; block partial sums of b.
 __global__ void __launch_bounds__(kBlock) k_node_rhs_mixed(SimConst K, const float* mom, double t,
                                                            double* rho, double* b, double* part,
+                                                           const double* x, double* resid,
                                                            const long long* tstep) {
   if (tstep) t = ((double)*tstep + 1.0) * K.dt;  // a captured step: the end of step *tstep
+  x = mem(K, x);
+  resid = mem(K, resid);
   mom = mem(K, mom);
   rho = mem(K, rho);
   b = mem(K, b);
@@ -223,6 +226,7 @@ __global__ void __launch_bounds__(kBlock) k_node_rhs_mixed(SimConst K, const flo
     bv = rhs_manufactured(K, i, j, k, t);
     if (K.p2f != 0.0) bv -= r / K.eps0;
     b[n] = bv;
+    if (resid) warm_residual(K, n, i, j, k, bv, x, resid);
   }
   double tot = block_sum(bv, sh);
   if (threadIdx.x == 0) part[blockIdx.x] = tot;
