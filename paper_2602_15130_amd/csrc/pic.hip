@@ -21,6 +21,7 @@
 #include "pic_direct.hpp"
 #include "pic_angles.hpp"
 #include "pic_collide_heavy.hpp"
+#include "pic_draw.hpp"
 #include "pic_order.hpp"
 #include "pic_host.hpp"
 
@@ -39,7 +40,7 @@ enum Arr {
   A_KEY, A_SLOT, A_TIDX, A_TKEY, A_D, A_U, A_V0G,
   A_COUNT, A_CSTART, A_BSUM, A_TILE, A_MOM, A_RHO, A_B, A_PHI, A_E, A_E32, A_CGV, A_LOW,
   A_PART_A, A_PART_B, A_EPART, A_NPART, A_NORMS, A_BAR, A_RESULT, A_FLAGS, A_CNT, A_CGIT, A_CGRR,
-  A_DEFER, A_STEPC, A_MIXC, A_DIRECT, A_CHECK, A_MEAN,
+  A_DEFER, A_STEPC, A_MIXC, A_DIRECT, A_CHECK, A_MEAN, A_NREC, A_SPREAD,
   A_NARR
 };
 
@@ -63,8 +64,13 @@ Layout make_layout(const pic_discretization* d, int precision) {
   b[A_OFF0] = b[A_OFF1] = b[A_VF0] = b[A_VF1] = b[A_ASF0] = b[A_ASF1] = 3 * pm * 4;
   b[A_KEY] = b[A_SLOT] = b[A_TIDX] = b[A_TKEY] = np * 4;
   b[A_D] = 3 * np * (f64 ? 8 : 4);
-  b[A_U] = 3 * np * 8;    // private collision copies; FP64 export of the mixed state
-  b[A_V0G] = 3 * np * 8;
+  // private collision copies; FP64 export of the mixed state; call B's and call
+  // A's drawn pairs, kRecCap per tile
+  const int64_t ntiles = (np + kTileB - 1) / kTileB;
+  static_assert(kRecCap * sizeof(PairRec<double>) <= 3 * kTileB * 8, "a tile's pairs fit its scratch");
+  b[A_U] = b[A_V0G] = 3 * ntiles * kTileB * 8;
+  b[A_NREC] = 2 * ntiles * 4;
+  b[A_SPREAD] = (int64_t)kCntSpread * kCntStride * 8;
   b[A_COUNT] = nn * 4;
   b[A_CSTART] = (nn + 1) * 4;
   b[A_BSUM] = (nscan + 1) * 4;
@@ -260,7 +266,6 @@ struct pic_ctx {
   float* Df{};
   bool fused = true;
   bool lean_pass = true;        // lean pass instance first, general one for the tiles it defers
-  bool sort_events = false;     // mixed pass instances that sort long event lists
   // Captured steps (pic_use_graphs): two steps per graph, one graph per
   // double-buffer parity, recorded on a private stream and replayed on the
   // context's stream; kernels then take the step from *stepc.
@@ -269,7 +274,8 @@ struct pic_ctx {
   hipStream_t cap_stream = nullptr;
   long long* stepc = nullptr;
   MixConst* mixc = nullptr;
-  int* defer = nullptr;         // the deferred tiles (count, done, list)
+  int* defer = nullptr;         // the deferred tiles (count, list)
+  int* nrec = nullptr;          // drawn pairs per tile and call
   void* mom{};
   double *rho{}, *b{}, *phi{}, *E{}, *cgv{}, *lowbuf{}, *partA{}, *partB{};
   float* E32{};
@@ -277,6 +283,7 @@ struct pic_ctx {
   unsigned* bar{};
   int *flags{}, *cgit{};
   unsigned long long* cnt{};
+  unsigned long long* spread{};
   // stage timing with HIP events on the context stream
   bool timing = false;
   uint32_t timing_mask = 0;  // stages timed while timing is on (bit 1 << stage)
@@ -627,7 +634,7 @@ int collide(pic_ctx* c, int call, int64_t step, double* D, long long* pairlog, i
     if (c->heavy_split > 1) TRY(fill<double>(c, D, 0.0, 3 * K.np));
     hfn<<<dim3(K.nn, c->heavy_split), kHeavyThreads, c->heavy_lds_n * 3 * sizeof(long long), c->stream>>>(
         K, call, step, c->v[c->cur], c->cstart, D, c->U, c->V0G, (unsigned*)c->tidx, c->heavy_lds_n,
-        c->heavy_bits, pairlog, cap, c->cnt, c->flags);
+        c->heavy_bits, pairlog, cap, c->cnt, c->spread, c->flags);
     if (c->heavy_split > 1)
       k_heavy_finish<<<grid_for(3 * K.np), kBlock, 0, c->stream>>>(K, D, c->heavy_bits);
     LAUNCH_CHECK(c, "collide (heavy)");
@@ -695,8 +702,12 @@ PartArgs part_args(pic_ctx* c) {
   a.gmark = c->tidx;  // the sort's index arrays are idle during the particle pass
   a.gtl = c->tkey;
   a.counters = c->cnt;
+  a.spread = c->spread;
   a.flags = c->flags;
   a.defer = c->defer;
+  a.recB = c->U;  // (idle until the general instance runs)
+  a.recA = c->V0G;
+  a.nrec = c->nrec;
   a.mixc = c->mixc;
   a.ntiles = (int)((c->K.np + kTileB - 1) / kTileB);
   a.defer_list = 0;
@@ -718,46 +729,45 @@ __global__ void k_step_consts(SimConst K, PartArgs a, MixConst* out) {
 __global__ void k_step_advance(long long* stepc) { *stepc += 1; }
 
 // Instances of the fused passes: the full one (angle and pair logs, the
-// anisotropic samplers), the general lean one and the lean one that leaves
-// the tiles it cannot run on lanes alone to the general one.
+// anisotropic samplers), the general one, and two that take the tiles they can
+// and leave the others to the general one: with pairs drawn before the pass (few
+// pairs per tile) or in chunks in the tile (many).
 using MixedFn = void (*)(SimConst, MixConst, PartArgs, float*, float*, const float*, const float*);
 using F64Fn = void (*)(SimConst, PartArgs);
 struct PassFns {
-  MixedFn mixed[3];      // full, general, fast
-  MixedFn mixed_dev[3];  // (none), general, fast of captured steps
-  F64Fn f64[3];
+  MixedFn mixed[4];      // full, general, drawn pairs, chunks
+  MixedFn mixed_dev[4];  // (none), then those of captured steps
+  F64Fn f64[4];
 };
-template <int FAM, int SIG, bool S>
-PassFns pass_fns() {
-  return {{k_particles_mixed<FAM, SIG, true, false>, k_particles_mixed<FAM, SIG, false, false, false, S>,
-           k_particles_mixed<FAM, SIG, false, true, false, S>},
-          {nullptr, k_particles_mixed<FAM, SIG, false, false, true, S>,
-           k_particles_mixed<FAM, SIG, false, true, true, S>},
-          {k_particles_f64<FAM, SIG, true, false>, k_particles_f64<FAM, SIG, false, false>,
-           k_particles_f64<FAM, SIG, false, true>}};
-}
 template <int FAM, int SIG>
-PassFns pass_fns(bool sort) {
-  return sort ? pass_fns<FAM, SIG, true>() : pass_fns<FAM, SIG, false>();
+PassFns pass_fns() {
+  return {{k_particles_mixed<FAM, SIG, true, false>, k_particles_mixed<FAM, SIG, false, false>,
+           k_particles_mixed<FAM, SIG, false, true, false, kPairsDrawn>,
+           k_particles_mixed<FAM, SIG, false, true, false, kPairsChunks>},
+          {nullptr, k_particles_mixed<FAM, SIG, false, false, true>,
+           k_particles_mixed<FAM, SIG, false, true, true, kPairsDrawn>,
+           k_particles_mixed<FAM, SIG, false, true, true, kPairsChunks>},
+          {k_particles_f64<FAM, SIG, true, false>, k_particles_f64<FAM, SIG, false, false>,
+           k_particles_f64<FAM, SIG, false, true, kPairsDrawn>,
+           k_particles_f64<FAM, SIG, false, true, kPairsChunks>}};
 }
-// sort: the mixed instances that sort long event lists (sort_events)
-PassFns select_pass(const SimConst& K, bool sort) {
+PassFns select_pass(const SimConst& K) {
   const int sig = K.sigma_model == 0 ? kSigPoly : (K.omega == 1.0 ? kSigMaxwell : kSigHS);
   if (K.family == 1) {
-    if (sig == kSigHS) return pass_fns<1, kSigHS>(sort);
-    if (sig == kSigMaxwell) return pass_fns<1, kSigMaxwell>(sort);
-    return pass_fns<1, kSigPoly>(sort);
+    if (sig == kSigHS) return pass_fns<1, kSigHS>();
+    if (sig == kSigMaxwell) return pass_fns<1, kSigMaxwell>();
+    return pass_fns<1, kSigPoly>();
   }
-  if (sig == kSigMaxwell) return pass_fns<0, kSigMaxwell>(sort);
-  return pass_fns<0, kSigPoly>(sort);
+  if (sig == kSigMaxwell) return pass_fns<0, kSigMaxwell>();
+  return pass_fns<0, kSigPoly>();
 }
 
 // Workgroups of the general instance that works through the deferred tiles.
 constexpr int kDeferGrid = 2048;
 
-// Fused pass: the lean instance over all tiles, then the general one over the
-// tiles it deferred; or the general (or full) instance alone, for logged runs,
-// collide-only calls and collision loads where most tiles would be deferred.
+// Fused pass: the drawn-pairs instance (lean_pass) or the chunks instance over
+// all tiles, then the general one over the tiles it left; or the full instance
+// alone, for logged runs.
 int launch_particles(pic_ctx* c, const PartArgs& a0) {
   const SimConst& K = c->K;
   PartArgs a = a0;
@@ -776,16 +786,24 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
     LAUNCH_CHECK(c, "paper drift term");
   }
   const int tiles = (int)((K.np + kTileB - 1) / kTileB);
-  const PassFns fns = select_pass(K, c->sort_events);
+  const PassFns fns = select_pass(K);
   // the collision-angle and pair-log recording and the anisotropic polar-angle
   // samplers are compiled only into the full instances
   const bool full = K.anglog != nullptr || a.pairlog != nullptr || K.chi_model != PIC_CHI_ISO ||
                     K.coding_error != 0;
-  const bool lean = c->lean_pass && !full && !(a.mode & kCollideOnly);
-  const int which = full ? 0 : 1;
+  const int first = c->lean_pass ? 2 : 3, last = full ? 0 : 1;
   PartArgs ag = a;
-  ag.defer_list = lean ? 1 : 0;
-  const dim3 grid_general = G(c, lean ? std::min(tiles, kDeferGrid) : tiles);
+  ag.defer_list = full ? 0 : 1;
+  const dim3 grid_last = G(c, full ? tiles : std::min(tiles, kDeferGrid));
+  if (!full && first == 2 && (K.collisions || (a.mode & kCollideOnly))) {
+    const int per = draw_tiles_per_wave((int64_t)tiles * c->members);
+    const dim3 gd = G(c, (unsigned)((tiles + kDrawWaves * per - 1) / (kDrawWaves * per)));
+    if (c->precision == PIC_MIXED)
+      k_draw_pairs<float><<<gd, 64 * kDrawWaves, 0, c->stream>>>(K, a, per);
+    else
+      k_draw_pairs<double><<<gd, 64 * kDrawWaves, 0, c->stream>>>(K, a, per);
+    LAUNCH_CHECK(c, "draw pairs");
+  }
   if (c->precision == PIC_MIXED) {
     const MixConst M = mix_const(K, a);  // (a captured step computes them on the device)
     const MixedFn* fm = fns.mixed;
@@ -799,23 +817,23 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
       fm = fns.mixed_dev;
     }
     const int s = c->cur;
-    if (lean) {
+    if (!full) {
       TRY(fill(c, c->defer, 0, 1));  // an empty deferral list
-      fm[2]<<<G(c, tiles), dim3(kTileThreads), 0, c->stream>>>(K, M, a, c->off[s], c->vf[s],
+      fm[first]<<<G(c, tiles), dim3(kTileThreads), 0, c->stream>>>(K, M, a, c->off[s], c->vf[s],
                                                               c->asf[s], c->E32);
       LAUNCH_CHECK(c, "particles (mixed, lean)");
     }
-    fm[which]<<<grid_general, dim3(kTileThreads), 0, c->stream>>>(K, M, ag, c->off[s], c->vf[s],
+    fm[last]<<<grid_last, dim3(kTileThreads), 0, c->stream>>>(K, M, ag, c->off[s], c->vf[s],
                                                                 c->asf[s], c->E32);
     LAUNCH_CHECK(c, "particles (mixed)");
     return PIC_OK;
   }
-  if (lean) {
+  if (!full) {
     TRY(fill(c, c->defer, 0, 1));  // an empty deferral list
-    fns.f64[2]<<<G(c, tiles), kTileThreads, 0, c->stream>>>(K, a);
+    fns.f64[first]<<<G(c, tiles), kTileThreads, 0, c->stream>>>(K, a);
     LAUNCH_CHECK(c, "particles (lean)");
   }
-  fns.f64[which]<<<grid_general, kTileThreads, 0, c->stream>>>(K, ag);
+  fns.f64[last]<<<grid_last, kTileThreads, 0, c->stream>>>(K, ag);
   LAUNCH_CHECK(c, "particles");
   return PIC_OK;
 }
@@ -935,6 +953,13 @@ int one_step(pic_ctx* c) {
   return PIC_OK;
 }
 
+// The pair counts into the counters, before the host reads those.
+int fold_counters(pic_ctx* c) {
+  k_fold_counters<<<G(c, 1), kCntSpread, 0, c->stream>>>(c->cnt, c->spread, c->mstride);
+  LAUNCH_CHECK(c, "fold counters");
+  return PIC_OK;
+}
+
 // Read back flags raised by earlier asynchronous work.
 int check_flags(pic_ctx* c) {
   HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -1044,6 +1069,7 @@ int errors_into(pic_ctx* c, pic_error_norms* out, double* epart, double* npart, 
   k_err_nodes<<<G(c, nbn), kBlock, 0, c->stream>>>(K, t, c->phi, npart);
   k_err_final<<<G(c, 1), kBlock, 0, c->stream>>>(K, epart, nbp, npart, nbn, norms);
   LAUNCH_CHECK(c, "errors");
+  TRY(fold_counters(c));  // (for the warning below)
   TRY(check_flags(c));
   for (int m = 0; m < c->members; ++m) {
     double h[14];
@@ -1148,21 +1174,17 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     c->heavy = heavy;
     c->heavy_bits = heavy_scale_bits(c->K.g_max, c->K.navg);
     if (heavy) c->fused = false;
-    // The lean pass runs a tile's outcomes on lanes only, which needs at most
-    // kSmallPairs pairs per outcome and kPool records per call; expected pool
-    // use per call of a tile is 2 N_pairs-mean N_avg (cells per tile).  Above
-    // the pool most tiles would be deferred, so the general instance runs
-    // alone.  PIC_LEAN_PASS=0/1 overrides.
-    const double need = 2.0 * pairs * (double)c->K.navg * ((double)kTileB / std::max(nbar, 1.0));
-    c->lean_pass = !c->K.collisions || need <= kPool;
+    // The lean pass takes its pairs from lists drawn before it, which hold
+    // kRecCap pairs per call of a tile; expected are N_pairs-mean N_avg (cells
+    // per tile).  Above half the list (the paper's densest cells have 1.7 times
+    // the mean's pairs per tile) the instance that draws its pairs in chunks in
+    // the tile runs instead.  Runs with the lists against chunks (ms; 64^3,
+    // initialisation and norms included): 0.06 pairs per outcome 19.7 / 27.8
+    // mixed and 28.7 / 40.5 FP64, 0.36 pairs 33.8 / 38.7 mixed.
+    // PIC_LEAN_PASS=0/1 overrides.
+    const double need = pairs * (double)c->K.navg * ((double)kTileB / std::max(nbar, 1.0));
+    c->lean_pass = !c->K.collisions || need <= 0.5 * kRecCap;
     if (const char* lp = std::getenv("PIC_LEAN_PASS")) c->lean_pass = lp[0] == '1';
-    // Events per call of a tile, N_avg (cells per tile) P(N_pairs > 0): the
-    // mixed pass sorts its lists for the cell threads where they are long
-    // (the FP64 pass always does).  PIC_SORT_EVENTS=0/1 overrides.
-    const double events = (double)c->K.navg * ((double)kTileB / std::max(nbar, 1.0)) *
-                          (1.0 - std::exp(-pairs));
-    c->sort_events = c->K.collisions && events > 16.0;
-    if (const char* se = std::getenv("PIC_SORT_EVENTS")) c->sort_events = se[0] == '1';
   }
   c->cg_tol = disc->cg_tol;
   c->cg_max_iter = disc->cg_max_iter;
@@ -1219,6 +1241,8 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
   c->mixc = carve<MixConst>(c, A_MIXC);
   c->K.stepc = c->stepc;
   c->check = carve<double>(c, A_CHECK);
+  c->nrec = carve<int>(c, A_NREC);
+  c->spread = carve<unsigned long long>(c, A_SPREAD);
 
   // Cooperative grid for the Poisson solver: one block per CU at most, never
   // more than the node count needs, and never more than can be co-resident.
@@ -1387,6 +1411,7 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     TRY(fill<int>(c, c->flags, 0, kFlagCount));
     TRY(fill<int>(c, c->defer, 0, 1));
     TRY(fill<unsigned long long>(c, c->cnt, 0ull, kCntCount));
+    TRY(fill<unsigned long long>(c, c->spread, 0ull, kCntSpread * kCntStride));
     c->count_zero = false;
     TRY(zero_counts(c));
     TRY(fill<double>(c, c->phi, 0.0, K.nn));
@@ -1496,6 +1521,7 @@ int pic_collide(pic_ctx* c, int call, double t, double* dv_avg, double* dv_src, 
                                                           dv_src);
     LAUNCH_CHECK(c, "source");
   }
+  TRY(fold_counters(c));  // (for the warning below)
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   if (pairlog_n) {
     unsigned long long nlog = 0;
@@ -1604,7 +1630,7 @@ int pic_checkpoint_save(pic_ctx* c, void* host_dst, int64_t bytes) {
     c->err = "checkpoint save: buffer size must equal pic_checkpoint_bytes";
     return PIC_EINVAL;
   }
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  TRY(fold_counters(c));
   TRY(check_flags(c));
   CkptHeader h{kCkptMagic, 1u, c->precision, c->cur, c->K.np, (int64_t)c->K.nn, c->step,
                c->K.seed, c->K.rep, c->K.navg, c->K.dt};
@@ -1637,6 +1663,7 @@ int pic_checkpoint_load(pic_ctx* c, const void* host_src, int64_t bytes) {
     c->err = "checkpoint load: the checkpoint belongs to another problem, seed or precision";
     return PIC_EINVAL;
   }
+  TRY(fold_counters(c));  // (the loaded counters replace all counted so far)
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->cur = h.cur;
   if (bytes != ckpt_bytes(c)) {
@@ -1721,6 +1748,7 @@ int pic_angle_errors(pic_ctx* c, double out[4], int64_t* n_records) {
 int pic_stats(pic_ctx* c, pic_stats_t* out) {
   if (!c || !c->ready) return PIC_ESTATE;
   if (!out) return PIC_EINVAL;
+  TRY(fold_counters(c));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   int it = 0;
   double rr = 0.0;

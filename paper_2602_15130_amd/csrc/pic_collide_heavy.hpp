@@ -71,7 +71,8 @@ template <int SIG, bool FULL>
 __global__ void __launch_bounds__(kHeavyThreads, 4)
     k_collide_heavy(SimConst K, int call, int64_t step, const double* v, const int* cstart,
                     double* D, double* u, double* w, unsigned* hpq, int lds_n, int scale_bits,
-                    long long* pairlog, int64_t cap, unsigned long long* counters, int* flags) {
+                    long long* pairlog, int64_t cap, unsigned long long* counters,
+                    unsigned long long* spread, int* flags) {
   extern __shared__ unsigned long long heavy_acc[];
   __shared__ HeavyLds W;
   const int64_t NP = K.np;
@@ -282,8 +283,7 @@ __global__ void __launch_bounds__(kHeavyThreads, 4)
     ngmx += __shfl_xor(ngmx, off);
   }
   if (lane == 0) {
-    if (nacc) atomicAdd(&counters[kCntAccepted], nacc);
-    if (ngmx) atomicAdd(&counters[kCntGmax], ngmx);
+    count_pairs(spread, nacc, ngmx);
   }
   if (!lds_acc) __threadfence();
   __syncthreads();

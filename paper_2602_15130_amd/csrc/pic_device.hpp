@@ -45,6 +45,7 @@ struct SimConst {
   uint64_t seed;
   uint32_t rep;
   double L[3], h[3], inv_h[3], ih2[3];
+  double inv_L[3], wave[3];  // 1 / L and 2 pi / L
   double qm;           // q/m, or 0 when the field does not act on the particles
   double p2f;          // 1 when the particles feed the Poisson source, else 0
   double q, eps0, T, vbar, phibar, rho_amp;
@@ -102,11 +103,28 @@ struct U64x4 {
   uint64_t w[4];
 };
 
-__host__ __device__ inline uint64_t mul_hi64(uint64_t a, uint64_t b) {
+// The 128-bit product of two 64-bit words from four 32 x 32 + 64 bit
+// multiply-adds (v_mad_u64_u32, a quarter-rate instruction, is what a random
+// block costs; high and low word taken apart need seven such multiplies).
+__host__ __device__ inline void mul_wide(uint64_t a, uint64_t b, uint64_t& hi, uint64_t& lo) {
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
+  const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+  const uint64_t p = (uint64_t)a0 * b0;
+  const uint64_t t = (uint64_t)a1 * b0 + (p >> 32);
+  const uint64_t u = (uint64_t)a0 * b1 + (uint32_t)t;
+  hi = (uint64_t)a1 * b1 + (t >> 32) + (u >> 32);
+  lo = (u << 32) | (uint32_t)p;
+}
+
+// a ^ b ^ c, one three-input bit operation per half on the GPU.
+__host__ __device__ inline uint64_t xor3(uint64_t a, uint64_t b, uint64_t c) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  return __umul64hi(a, b);
+  const uint32_t lo = __builtin_amdgcn_bitop3_b32((uint32_t)a, (uint32_t)b, (uint32_t)c, 0x96);
+  const uint32_t hi = __builtin_amdgcn_bitop3_b32((uint32_t)(a >> 32), (uint32_t)(b >> 32),
+                                                  (uint32_t)(c >> 32), 0x96);
+  return ((uint64_t)hi << 32) | lo;
 #else
-  return (uint64_t)(((unsigned __int128)a * b) >> 64);
+  return a ^ b ^ c;
 #endif
 }
 
@@ -115,9 +133,10 @@ __host__ __device__ inline U64x4 philox(uint64_t c0, uint64_t c1, uint64_t c2, u
   const uint64_t m0 = 0xD2E7470EE14C6C93ull, m1 = 0xCA5A826395121157ull;
 #pragma unroll
   for (int round = 0; round < 10; ++round) {
-    uint64_t h0 = mul_hi64(m0, c0), l0 = m0 * c0;
-    uint64_t h1 = mul_hi64(m1, c2), l1 = m1 * c2;
-    uint64_t a = h1 ^ c1 ^ k0, b = h0 ^ c3 ^ k1;
+    uint64_t h0, l0, h1, l1;
+    mul_wide(m0, c0, h0, l0);
+    mul_wide(m1, c2, h1, l1);
+    uint64_t a = xor3(h1, c1, k0), b = xor3(h0, c3, k1);
     c0 = a; c1 = l1; c2 = b; c3 = l0;
     k0 += 0x9E3779B97F4A7C15ull;
     k1 += 0xBB67AE8584CAA73Bull;
@@ -136,7 +155,7 @@ __device__ inline double unif(uint64_t w) { return (double)(w >> 11) * 0x1.0p-53
 __device__ inline double unif_open(uint64_t w) { return ((double)(w >> 12) + 0.5) * 0x1.0p-52; }
 __device__ inline float unif32(uint64_t w) { return (float)(uint32_t)(w >> 40) * 0x1.0p-24f; }
 __device__ inline int index_below(uint64_t w, int n) {
-  return (int)__umul64hi(w & ~0x7FFull, (uint64_t)n);
+  return (int)__umul64hi(w & ~0x7FFull, (uint64_t)(uint32_t)n);
 }
 
 // ---------------------------------------------------------------------------
@@ -363,9 +382,8 @@ __device__ inline void phiM_factors(const SimConst& K, const double x[3], double
                                     double c[3]) {
   const double shift[3] = {1.0 / 7.0, 1.0 / 5.0, 1.0 / 3.0};
   for (int d = 0; d < 3; ++d) {
-    double arg = 2.0 * (x[d] / K.L[d] - shift[d]);
-    s[d] = sinpi(arg);
-    c[d] = cospi(arg);
+    double arg = 2.0 * (x[d] * K.inv_L[d] - shift[d]);
+    sincospi(arg, &s[d], &c[d]);
   }
 }
 
@@ -377,7 +395,7 @@ __device__ inline double phiM(const SimConst& K, const double x[3], double t) {
 
 __device__ inline double lap_phiM(const SimConst& K, const double x[3], double t) {
   double k2 = 0.0;
-  for (int d = 0; d < 3; ++d) k2 += (2.0 * kPi / K.L[d]) * (2.0 * kPi / K.L[d]);
+  for (int d = 0; d < 3; ++d) k2 += K.wave[d] * K.wave[d];
   return -k2 * phiM(K, x, t);
 }
 
@@ -385,9 +403,9 @@ __device__ inline void EM(const SimConst& K, const double x[3], double t, double
   double s[3], c[3];
   phiM_factors(K, x, s, c);
   double a = K.phibar * exp(0.5 * t / K.T);
-  E[0] = -a * (2.0 * kPi / K.L[0]) * c[0] * s[1] * s[2];
-  E[1] = -a * (2.0 * kPi / K.L[1]) * s[0] * c[1] * s[2];
-  E[2] = -a * (2.0 * kPi / K.L[2]) * s[0] * s[1] * c[2];
+  E[0] = -a * K.wave[0] * c[0] * s[1] * s[2];
+  E[1] = -a * K.wave[1] * s[0] * c[1] * s[2];
+  E[2] = -a * K.wave[2] * s[0] * s[1] * c[2];
 }
 
 // Cross-section models known at compile time in the fused kernels.
@@ -414,7 +432,8 @@ __device__ inline double sigma_g(const SimConst& K, double g) {
 
 // Hard sphere, Gaussian partners: int g (v_q - v_p) f_v = -s^2 K(l) v_p/|v_p|.
 // K(l) = [(l^4 + 2l^2 - 1) erf(l/sqrt2) + 2l(l^2+1) phi_N(l)] / l^2, summed as a
-// power series below l = 0.5 where the closed form cancels.
+// power series below l = 0.5 where the closed form cancels (eleven terms: from
+// the tenth on they no longer change the rounded sum).
 __device__ inline double hs_kernel(double l) {
   if (l < 0.5) {
     // erf(l/sqrt2) = sqrt(2/pi) sum a_n l^(2n+1); 2 l phi_N(l) = sqrt(2/pi) sum b_n l^(2n+1)
@@ -423,7 +442,7 @@ __device__ inline double hs_kernel(double l) {
     double bm2 = 0.0, am2 = 0.0;         // n = j-2
     double bm1 = 1.0, am1 = 1.0;         // n = j-1 (j = 1)
     double sum = 0.0, l2 = l * l, lp = l;  // l^(2j-1)
-    for (int j = 1; j < 30; ++j) {
+    for (int j = 1; j < 12; ++j) {
       double bj = bm1 * (-0.5) / j, aj = bj / (2.0 * j + 1.0);
       sum += (am2 + 2.0 * am1 - aj + bm1 + bj) * lp;
       am2 = am1; bm2 = bm1; am1 = aj; bm1 = bj;
@@ -457,8 +476,8 @@ __device__ inline void source_integral(const SimConst& K, const double u[3], dou
       return;
     }
     double s = K.vbar;
-    double kk = hs_kernel(sp / s);
-    for (int i = 0; i < 3; ++i) out[i] = -K.sigma_ref * s * s * kk * u[i] / sp;
+    const double f = -K.sigma_ref * s * s * hs_kernel(sp * K.inv_vbar) / sp;
+    for (int i = 0; i < 3; ++i) out[i] = f * u[i];
     return;
   }
   poly_source(K, u, t, out);
@@ -526,8 +545,8 @@ __device__ inline void source_integral_t(const SimConst& K, const double u[3], d
       return;
     }
     double s = K.vbar;
-    double kk = hs_kernel(sp / s);
-    for (int i = 0; i < 3; ++i) out[i] = -K.sigma_ref * s * s * kk * u[i] / sp;
+    const double f = -K.sigma_ref * s * s * hs_kernel(sp * K.inv_vbar) / sp;
+    for (int i = 0; i < 3; ++i) out[i] = f * u[i];
   } else {
     poly_source_inl(K, u, t, out);
   }

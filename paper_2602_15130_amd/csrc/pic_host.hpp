@@ -46,6 +46,8 @@ inline SimConst derive(const pic_problem* p, const pic_discretization* d, uint64
     K.h[k] = p->L[k] / d->ncell[k];
     K.inv_h[k] = (double)d->ncell[k] / p->L[k];
     K.ih2[k] = 1.0 / (K.h[k] * K.h[k]);
+    K.inv_L[k] = 1.0 / p->L[k];
+    K.wave[k] = 2.0 * kPi / p->L[k];
   }
   K.qm = p->field_to_particles ? p->q / p->m : 0.0;
   K.p2f = p->particles_to_field ? 1.0 : 0.0;

@@ -37,6 +37,25 @@ constexpr int kLdsSlots = PIC_LDS_SLOTS;          // LDS-resident slots per tile
 #ifndef PIC_F64_LEAN_WAVES
 #define PIC_F64_LEAN_WAVES 4
 #endif
+// The instances whose pairs are drawn before the pass (registers without spills,
+// but for one in the paper family's mixed form; the FP64 source of the paper family
+// needs more), and those that draw chunks in the tile (31 KB of LDS a tile in
+// the mixed form, 48 KB in FP64).
+#ifndef PIC_MIXED_REC_WAVES
+#define PIC_MIXED_REC_WAVES 8
+#endif
+#ifndef PIC_F64_REC_WAVES
+#define PIC_F64_REC_WAVES 4
+#endif
+#ifndef PIC_F64_REC_PAPER_WAVES
+#define PIC_F64_REC_PAPER_WAVES 3
+#endif
+#ifndef PIC_MIXED_DENSE_WAVES
+#define PIC_MIXED_DENSE_WAVES 4
+#endif
+#ifndef PIC_F64_DENSE_WAVES
+#define PIC_F64_DENSE_WAVES 3
+#endif
 
 // Flags raised by kernels and read back at the next synchronising call.
 enum { kFlagCgNoConv = 0, kFlagBarrier = 1, kFlagNonFinite = 2, kFlagCapacity = 3, kFlagCount = 4 };
@@ -47,6 +66,19 @@ constexpr int64_t kMaxPairsPerOutcome = int64_t(1) << 22;
 constexpr int kMaxStableCell = 1 << 16;
 // 64-bit counters: accepted collisions, candidate pairs with g > g_max, pair-log records.
 enum { kCntAccepted = 0, kCntGmax = 1, kCntPairLog = 2, kCntAngles = 3, kCntCount = 4 };
+// The kernels add the first two to one of kCntSpread pairs of words, by workgroup,
+// and k_fold_counters gathers them when they are read: additions to one address
+// take ~8 ns each, one after another, and at two a tile they bounded the whole
+// mixed pass (64^3, 32,768 tiles: 540 us with one address, 275 with these).
+constexpr int kCntSpread = 512;
+constexpr int kCntStride = 8;  // words between two pairs (64 bytes)
+__device__ inline void count_pairs(unsigned long long* spread, unsigned long long accepted,
+                                   unsigned long long over_gmax) {
+  unsigned long long* c =
+      spread + ((blockIdx.x + 61u * blockIdx.y) % (unsigned)kCntSpread) * kCntStride;
+  if (accepted) atomicAdd(&c[kCntAccepted], accepted);
+  if (over_gmax) atomicAdd(&c[kCntGmax], over_gmax);
+}
 
 // ---------------------------------------------------------------------------
 // Block reductions with a fixed combination order (bitwise reproducible).
@@ -123,6 +155,19 @@ __global__ void k_fill(T* p, T v, int64_t n, int64_t mstride) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
+}
+
+// Moves the spread counts into the counters (one workgroup per member).
+__global__ void __launch_bounds__(kCntSpread) k_fold_counters(unsigned long long* cnt,
+                                                              unsigned long long* spread,
+                                                              int64_t mstride) {
+  cnt = mem_z(mstride, cnt);
+  spread = mem_z(mstride, spread);
+  unsigned long long* c = spread + threadIdx.x * kCntStride;
+  for (int i = 0; i < 2; ++i) {
+    if (c[i]) atomicAdd(&cnt[i], c[i]);
+    c[i] = 0ull;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1098,7 +1143,7 @@ __global__ void __launch_bounds__(kBlock) k_source_f64(SimConst K, const double*
   int c = key[i];
   int n = cstart[c + 1] - cstart[c];
   double u[3] = {v[i], v[K.np + i], v[2 * K.np + i]}, I[3] = {0, 0, 0};
-  double coef = (K.w * K.dt * (double)(n - 1)) / (2.0 * K.dV);
+  double coef = K.src_half * (double)(n - 1);
   if (n >= 2) source_integral(K, u, t, I);
   for (int d = 0; d < 3; ++d) S[d * K.np + i] = (n >= 2) ? coef * I[d] : 0.0;
 }
@@ -1150,7 +1195,7 @@ __global__ void __launch_bounds__(kBlock) k_kick_f64(SimConst K, double t, doubl
     int cc = key[i];
     int n = cstart[cc + 1] - cstart[cc];
     double I[3] = {0, 0, 0};
-    double coef = (K.w * K.dt * (double)(n - 1)) / (2.0 * K.dV);
+    double coef = K.src_half * (double)(n - 1);
     if (n >= 2) source_integral(K, vp, t_src, I);
     for (int d = 0; d < 3; ++d) coll[d] = D[d * NP + i] - ((n >= 2) ? coef * I[d] : 0.0);
   }

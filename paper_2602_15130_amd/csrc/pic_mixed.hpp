@@ -232,11 +232,12 @@ __global__ void __launch_bounds__(kBlock) k_node_rhs_mixed(SimConst K, const flo
   if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
-// Hard-sphere kernel K(l) in FP32 (series below 0.5, closed form above).
+// Hard-sphere kernel K(l) in FP32 (series below 0.5, closed form above; the fifth
+// term no longer changes the rounded sum).
 __device__ inline float hs_kernel_f(float l) {
   if (l < 0.5f) {
     float bm2 = 0.0f, am2 = 0.0f, bm1 = 1.0f, am1 = 1.0f, sum = 0.0f, l2 = l * l, lp = l;
-    for (int j = 1; j < 10; ++j) {
+    for (int j = 1; j < 6; ++j) {
       float bj = bm1 * (-0.5f) / (float)j, aj = bj / (2.0f * j + 1.0f);
       sum += (am2 + 2.0f * am1 - aj + bm1 + bj) * lp;
       am2 = am1; bm2 = bm1; am1 = aj; bm1 = bj;
@@ -355,13 +356,17 @@ __device__ inline void EM_mixed(const MixConst& M, int ci, int cj, int ck, const
 // The mixed-form fused pass, same phases as the FP64 one.  FAM: 0 the paper's
 // manufactured family (time-dependent velocity distribution; the drift's
 // manufactured term comes from k_paper_drift_mixed), 1 the configuration
-// family.  Registers are capped for six waves per SIMD (measured best at 64^3:
-// the pass is latency bound, and the extra resident waves outweigh the spills).
+// family.  Registers are capped for as many waves per SIMD as LDS allows without
+// spills worth mentioning: eight with the pairs drawn before the pass (59 VGPRs,
+// 17 KB of LDS a tile), four with chunks.
 // DEVC: the instances of captured steps, which take the pass's constants
-// from the device (written by k_step_consts) instead of the argument.  SORT:
-// long event lists are sorted for the cell threads (sorted_list).
-template <int FAM, int SIG, bool FULL, bool FAST, bool DEVC = false, bool SORT = true>
-__global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PIC_MIXED_WAVES) k_particles_mixed(SimConst K, MixConst M, PartArgs a,
+// from the device (written by k_step_consts) instead of the argument.  PAIRS:
+// where the pairs come from.
+template <int FAM, int SIG, bool FULL, bool FAST, bool DEVC = false, int PAIRS = kPairsInTile>
+__global__ void __launch_bounds__(kTileThreads, PAIRS == kPairsDrawn    ? PIC_MIXED_REC_WAVES
+                                                : PAIRS == kPairsChunks ? PIC_MIXED_DENSE_WAVES
+                                                : FAST                  ? PIC_MIXED_LEAN_WAVES
+                                                                        : PIC_MIXED_WAVES) k_particles_mixed(SimConst K, MixConst M, PartArgs a,
                                                             float* off, float* vf, const float* ash,
                                                             const float* E32) {
   a = member_view(K, a);
@@ -378,14 +383,15 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
   // (the velocity shape is read once, in the drift, straight from memory), and
   // the field acceleration kept from kick B for kick A; the copy-on-write
   // scratch of outcomes run by a cell thread is global.
-  __shared__ float lv0[3 * kLdsSlots], lD[3 * kLdsSlots], loff[3 * kLdsSlots],
+  constexpr bool REC = PAIRS == kPairsDrawn, DENSE = PAIRS == kPairsChunks;
+  static_assert(PAIRS == kPairsInTile || FAST, "these take the tiles they can and leave the others");
+  __shared__ float lv0[3 * kLdsSlots], lD[REC ? 1 : 3 * kLdsSlots], loff[3 * kLdsSlots],
       lacc[3 * kLdsSlots];
   __shared__ int lkey[kLdsSlots];
   __shared__ int lcs[kCellCache + 1];  // cell starts of a tile of at most kCellCache cells
-  // (the general instance, which takes the dense tiles, has the larger record
-  // pool; the full one keeps the small pool and its occupancy)
-  __shared__ CollideLds<float, 2, 128, (FAST || FULL) ? kPool : kPoolGeneral> cl;  // both calls drawn up front
-  __shared__ int sh_i[4];
+  __shared__ PassLds<float, CollideLds<float, 2, 128, (FAST || FULL) ? kPool : kPoolGeneral>, PAIRS> cu;
+  auto& cl = cu.lists();
+  __shared__ int sh_i[6];
   const int tid = threadIdx.x;
   const int NP = (int)K.np;
   auto tile = [&](const int b) __attribute__((always_inline)) {
@@ -394,16 +400,24 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
       sh_i[1] = min(a.tile_c0[b + 1], K.nn);
       sh_i[2] = a.tile_s0[b];
       sh_i[3] = a.tile_s0[b + 1];
-      tile_lists_clear(cl);
+      if constexpr (REC) tile_records(a, b, K.collisions || (a.mode & kCollideOnly), sh_i + 4);
+      else if constexpr (!DENSE) tile_lists_clear(cl);
     }
+    if constexpr (REC) cu.clear_ranges();
     __syncthreads();
     const int c0 = sh_i[0], ncells = max(sh_i[1] - sh_i[0], 0), s0 = sh_i[2], ns = sh_i[3] - sh_i[2];
     if (ns <= 0) return;
-    if (FAST && ns > kLdsSlots) {  // (uniform) the general instance takes this tile
-      defer_tile(a, b);
+    const bool coll = K.collisions || (a.mode & kCollideOnly);
+    if (FAST && (ns > kLdsSlots || (REC && coll && min(sh_i[4], sh_i[5]) < 0))) {
+      defer_tile(a, b);  // (uniform) the general instance takes this tile
       return;
     }
     const bool lds = FAST || ns <= kLdsSlots;
+    if constexpr (DENSE)
+      if (coll && !dense_fits(K, a, c0, ncells, cu.chunk)) {
+        defer_tile(a, b);  // (uniform)
+        return;
+      }
     const int st = lds ? kLdsSlots : NP;
     float* v0 = lds ? lv0 : (float*)a.gv0 + s0;
     float* D = lds ? lD : (float*)a.gD + s0;
@@ -433,8 +447,12 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
     const bool pre = lds && !(a.mode & kCollideOnly);
     const bool reuse_A = pre && (!(a.mode & kDoB) || a.na == a.nb + 1);
     const float* amp0 = (a.mode & kDoB) ? M.emB : M.emA;
-    const bool pass_coll = K.collisions && !(a.mode & kCollideOnly);
-    if (pass_coll) tile_zero_D(ns, st, D);
+    if (coll && !REC) tile_zero_D(ns, st, D);
+    PairRec<float> rec;  // REC: this thread's pair of the call that runs next
+    auto load_pairs = [&](int li, const void* list) {
+      if constexpr (REC) cu.load(li, (const PairRec<float>*)list + (int64_t)b * kRecCap, sh_i[4 + li], rec);
+    };
+    if (REC && coll) load_pairs((a.mode & kDoB) ? 0 : 1, (a.mode & kDoB) ? a.recB : a.recA);
     for (int j = tid; j < ns; j += kTileThreads) {
       const int p = s0 + j;
       for (int d = 0; d < 3; ++d) v0[d * st + j] = vf[(int64_t)d * NP + p];
@@ -453,13 +471,36 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
     const bool few_cells = ncells <= kCellCache;
     if (few_cells)
       for (int i = tid; i <= ncells; i += kTileThreads) lcs[i] = a.cstart[c0 + i];
-    if (pass_coll) tile_draw_pass(K, a, c0, ncells, cl);
+    if constexpr (!REC && !DENSE)
+      if (coll && !(a.mode & kCollideOnly)) tile_draw_pass(K, a, c0, ncells, cl);
     __syncthreads();
-    if (FAST && pass_coll &&
-        !tile_lane_only(cl, (a.mode & kDoB) ? 0 : 1, (a.mode & kDoA) ? 2 : 1)) {
-      defer_tile(a, b);  // (uniform, and nothing written to memory yet)
-      return;
-    }
+    if constexpr (FAST && !REC && !DENSE)
+      if (coll && !tile_lane_only(cl, (a.mode & kDoB) ? 0 : 1, (a.mode & kDoA) ? 2 : 1)) {
+        defer_tile(a, b);  // (uniform, and nothing written to memory yet)
+        return;
+      }
+    // one call on v0: li (0 B, 1 A or the collide-only one)
+    auto run_call = [&](int li) __attribute__((always_inline)) {
+      const int call = li ? a.callA : a.callB;
+      const int64_t step = li ? a.na : a.nb;
+      if constexpr (REC) {
+        cu.template apply<SIG>(K, a, (const PairRec<float>*)(li ? a.recA : a.recB) + (int64_t)b * kRecCap,
+                               sh_i[4 + li], rec, v0, st);
+      } else if constexpr (DENSE) {
+        tile_dense<SIG, float>(K, a, call, step, c0, ncells, s0, ns, v0, D, lkey, st, cu.chunk);
+      } else {
+        if constexpr (!FAST) {
+          if (a.mode & kCollideOnly) {
+            tile_collide<SIG, float, FULL>(K, a, call, step, c0, ncells, s0, ns, v0, u, D, mark, tl, 0, st,
+                                           NP, cl);
+            return;
+          }
+        }
+        tile_run<SIG, float, FULL, FAST, true>(K, a, li, call, step, c0, ncells, s0, ns, v0, u, D, mark,
+                                               tl, li ? K.navg : 0, st, NP, cl,
+                                               few_cells ? lcs : nullptr);
+      }
+    };
     auto cell_count = [&](int j) {
       const int c = tk[j];
       if (few_cells) return lcs[c - c0 + 1] - lcs[c - c0];
@@ -474,7 +515,8 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
     // Half kick of slot j: v += (acc + <dv> - <dv^M>) / 2, plus (paper family)
     // the manufactured term hman a with the particle's velocity shape a; h2 is
     // (vhat / vbar)^2 at the call's source time.
-    auto kick_with = [&](int j, const float acc[3], bool coll_on, const float* h2,
+    // li: the call (0 B, 1 A).
+    auto kick_with = [&](int j, const float acc[3], bool coll_on, int li, const float* h2,
                          const float* hman, const float* sa) {
       float vp[3] = {v0[j], v0[st + j], v0[2 * st + j]};
       float coll[3] = {0.0f, 0.0f, 0.0f};
@@ -483,9 +525,14 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
         float I[3] = {0.0f, 0.0f, 0.0f};
         float coef = M.src_w * (float)(n - 1);
         if (n >= 2) source_integral_f<FAM, SIG>(K, M, h2, vp, I);
+        float Dj[3] = {0.0f, 0.0f, 0.0f};  // N_avg <dv>
+        if constexpr (REC) slot_changes(cu.P, cu.cr[li], sh_i[4 + li], tk[j] - c0, j, Dj);
         for (int d = 0; d < 3; ++d) {
-          coll[d] = D[d * st + j] * inv_navg - ((n >= 2) ? coef * I[d] : 0.0f);
-          D[d * st + j] = 0.0f;  // cleared for the next call (a barrier follows every kick)
+          if (!REC) {
+            Dj[d] = D[d * st + j];
+            D[d * st + j] = 0.0f;  // cleared for the next call (a barrier follows every kick)
+          }
+          coll[d] = Dj[d] * inv_navg - ((n >= 2) ? coef * I[d] : 0.0f);
         }
       }
       for (int d = 0; d < 3; ++d) {
@@ -496,16 +543,17 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
       }
     };
 
-    if (!FAST && (a.mode & kCollideOnly)) {  // (the lean instance never runs collide-only)
-      tile_collide<SIG, float, FULL>(K, a, a.callA, a.na, c0, ncells, s0, ns, v0, u, D, mark, tl, 0, st,
-                               NP, cl);
+    if constexpr (!FAST || REC || DENSE) if (a.mode & kCollideOnly) {
+      run_call(1);
       for (int j = tid; j < ns; j += kTileThreads) {
         int n = cell_count(j);
-        float vp[3] = {v0[j], v0[st + j], v0[2 * st + j]}, I[3] = {0, 0, 0};
+        float vp[3] = {v0[j], v0[st + j], v0[2 * st + j]}, I[3] = {0, 0, 0}, Dj[3] = {0, 0, 0};
         float coef = M.src_w * (float)(n - 1);
         if (n >= 2) source_integral_f<FAM, SIG>(K, M, M.h2A, vp, I);
+        if constexpr (REC) slot_changes(cu.P, cu.cr[1], sh_i[5], tk[j] - c0, j, Dj);
         for (int d = 0; d < 3; ++d) {
-          a.Dout[(int64_t)d * NP + s0 + j] = (double)(D[d * st + j] * inv_navg);
+          if (!REC) Dj[d] = D[d * st + j];
+          a.Dout[(int64_t)d * NP + s0 + j] = (double)(Dj[d] * inv_navg);
           a.Sout[(int64_t)d * NP + s0 + j] = (n >= 2) ? (double)(coef * I[d]) : 0.0;
         }
       }
@@ -513,9 +561,8 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
     }
 
     if (a.mode & kDoB) {  // call B at t^{nb+1/2}, second half kick at t^{nb+1}
-      if (K.collisions)
-        tile_run<SIG, float, FULL, FAST, SORT>(K, a, 0, a.callB, a.nb, c0, ncells, s0, ns, v0, u, D, mark, tl, 0, st,
-                                 NP, cl, few_cells ? lcs : nullptr);
+      if (coll) run_call(0);
+      if (REC && coll && (a.mode & kDoA)) load_pairs(1, a.recA);
       for (int j = tid; j < ns; j += kTileThreads) {
         float acc[3], sa[3] = {0.0f, 0.0f, 0.0f};
         if constexpr (FAM == 0) {
@@ -527,9 +574,10 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
         } else {
           field_acc(j, M.emB, acc);
         }
-        kick_with(j, acc, K.collisions != 0, M.h2B, M.hB, sa);
+        kick_with(j, acc, K.collisions != 0, 0, M.h2B, M.hB, sa);
       }
-      if (tid == 0) cl.pool_n = 0;
+      if constexpr (!REC && !DENSE)
+        if (tid == 0) cl.pool_n = 0;
       __syncthreads();
       if (!(a.mode & kDoA)) {
         for (int j = tid; j < ns; j += kTileThreads)
@@ -539,9 +587,7 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
     }
 
     // call A at t^{na}, first half kick, drift to t^{na+1}
-    if (K.collisions)
-      tile_run<SIG, float, FULL, FAST, SORT>(K, a, 1, a.callA, a.na, c0, ncells, s0, ns, v0, u, D, mark, tl, K.navg,
-                               st, NP, cl, few_cells ? lcs : nullptr);
+    if (coll) run_call(1);
     for (int base = 0; base < ns; base += kTileThreads) {
       int j = base + tid;
       bool valid = j < ns;
@@ -556,7 +602,7 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_MIXED_LEAN_WAVES : PI
         } else {
           field_acc(j, M.emA, acc);
         }
-        kick_with(j, acc, K.collisions != 0, M.h2A, M.hA, sa);
+        kick_with(j, acc, K.collisions != 0, 1, M.h2A, M.hA, sa);
         int c = tk[j];
         int cc[3];
         node_coords(K, c, cc[0], cc[1], cc[2]);

@@ -11,7 +11,12 @@
 // fewer than B + (largest cell) particles; per-particle working arrays live in
 // LDS when they fit and in global scratch otherwise.
 //
-// Collisions in a tile: (1) one lane per (cell, outcome) draws N_pairs
+// Collisions in a tile: where the pairs are few they were drawn before the pass
+// (k_draw_pairs) and one thread per outcome applies them; where they are many
+// the tile draws them in chunks (tile_dense); each slot's thread then adds up the
+// changes of its own slot in outcome order.  The full and general instances
+// (logs, anisotropic scattering, tiles beyond the LDS slots, outcomes of more than
+// 64 pairs) run event lists instead: (1) one lane per (cell, outcome) draws N_pairs
 // (Algorithm 1) and records the few lanes that have candidate pairs; (2) one
 // lane per such outcome with at most kSmallPairs pairs runs it on a private
 // list of the velocities it changes and stores the changes; (3) one thread per
@@ -27,7 +32,7 @@
 namespace pic {
 
 constexpr int kSmallPairs = 4;    // outcomes with at most this many pairs run one per lane
-constexpr int kPool = 128;        // velocity-change records of those outcomes per tile (lean instances)
+constexpr int kPool = 128;        // velocity-change records of those outcomes per tile
 constexpr int kPoolGeneral = 512; // the same in the mixed general instances, which take the dense tiles
 constexpr int kCellCache = 64;    // cells of a tile whose starts the mixed pass keeps in LDS
 
@@ -51,6 +56,48 @@ struct CollideLds {
   int need[NL], big[NL];  // pool records the list's outcomes need; an outcome over kSmallPairs
   int pslot[POOL];
   R pdv[3 * POOL];  // [3][POOL]
+};
+
+// One candidate pair of a call, drawn apart from its application: the tile's
+// slots of its two particles (slot p | slot q << 16), the tile's cell it belongs
+// to, the pairs of its outcome and its place among them (cell << 16 | pairs << 8
+// | place), the accept uniform and the scattering direction (eq. n).  The pairs
+// of a call stand in increasing (cell, outcome, place).
+template <class R>
+struct PairRec {
+  unsigned pq, info;
+  R u, n[3];
+};
+// Where a pass instance takes its pairs from: event lists drawn in the tile and
+// run as such (tile_draw, tile_run), the lists of k_draw_pairs, or chunks drawn in
+// the tile (tile_dense).
+enum { kPairsInTile = 0, kPairsDrawn = 1, kPairsChunks = 2 };
+constexpr int kRecCap = 128;       // records of one call that a tile may have (record instances)
+constexpr unsigned kNoSlot = 0xffffu;
+// Velocity changes of the pairs held at once: two per pair (entries 2 r and 2 r + 1
+// belong to pair r, an outcome fills its pairs' entries from the front).
+template <class R, int PAIRS>
+struct PairLds {
+  R dv[3][2 * PAIRS];
+  union {
+    unsigned short slot[2 * PAIRS];
+    unsigned slot2[PAIRS];  // both entries of a pair
+  };
+};
+// The pairs [lo, hi) of each of a tile's first kCellCache cells.
+struct CellRanges {
+  short lo[kCellCache], hi[kCellCache];
+};
+// LDS of a call that draws and applies its pairs in chunks (tile_dense).
+constexpr int kDenseChunk = 256;   // pairs of a chunk, one per thread
+constexpr int kDenseMaxPairs = 64; // pairs of an outcome at most
+template <class R>
+struct DenseLds {
+  PairLds<R, kDenseChunk> P;
+  CellRanges cr;
+  PairRec<R> rec[kDenseChunk];
+  int wsum[kDenseChunk / 64], smax;
+  int accepted, over_gmax;
 };
 
 enum { kDoB = 1, kDoA = 2, kCollideOnly = 4 };
@@ -77,12 +124,17 @@ struct PartArgs {
   long long* pairlog;
   int64_t cap;
   unsigned long long* counters;
+  unsigned long long* spread;  // the pair counts by workgroup (null: in counters themselves)
   int* flags;
   // tiles the lean instance leaves to the general one: [0] count, [1] workgroups
   // done with the list, [2 ..] tile indices; the general instance works through
   // the list when defer_list is set, else through all tiles
   int* defer;
   int ntiles, defer_list;
+  // pairs drawn before the pass (record instances): call B's and call A's, [ntiles][kRecCap]
+  // of PairRec, and their numbers [ntiles][2] (-1: the tile does not fit)
+  void *recB, *recA;
+  int* nrec;
   // captured steps: nb = *K.stepc, na = nb + 1; the mixed pass reads its FP32
   // constants from mixc, written by k_step_consts before every pass
   int step_dev;
@@ -119,11 +171,25 @@ __device__ inline PartArgs member_view(const SimConst& K, PartArgs a) {
   a.gmark = mem(K, a.gmark);
   a.gtl = mem(K, a.gtl);
   a.counters = mem(K, a.counters);
+  a.spread = mem(K, a.spread);
   a.flags = mem(K, a.flags);
   a.defer = mem(K, a.defer);
+  a.recB = mem(K, (char*)a.recB);
+  a.recA = mem(K, (char*)a.recA);
+  a.nrec = mem(K, a.nrec);
   a.mdrift = mem(K, a.mdrift);
   a.mdrift32 = mem(K, a.mdrift32);
   return a;
+}
+
+// Accepted pairs and pairs over g_max of this thread.
+__device__ inline void count_pairs(const PartArgs& a, unsigned long long acc, unsigned long long gmx) {
+  if (a.spread) {
+    count_pairs(a.spread, acc, gmx);
+    return;
+  }
+  if (acc) atomicAdd(&a.counters[kCntAccepted], acc);
+  if (gmx) atomicAdd(&a.counters[kCntGmax], gmx);
 }
 
 // Hands tile b to the general instance (thread 0; the caller returns uniformly).
@@ -358,6 +424,245 @@ __device__ inline int ntc_outcome_small(const SimConst& K, int cell, int64_t ste
   return cnt;
 }
 
+// Pair m of outcome k on cell c (n particles, the tile's slots from cs): its
+// two random blocks, all that does not depend on a velocity.
+template <class R>
+__device__ __attribute__((always_inline)) inline PairRec<R> draw_pair(const SimConst& K, int c, int ci, int cs, int n, int64_t step,
+                                       int call, int k, int m, int np) {
+  const U64x4 wa = stream_block(K, (uint64_t)c, (uint64_t)step, kTagColl, (uint64_t)call,
+                                (uint64_t)k, (uint64_t)(1 + 2 * m));
+  const U64x4 wb = stream_block(K, (uint64_t)c, (uint64_t)step, kTagColl, (uint64_t)call,
+                                (uint64_t)k, (uint64_t)(2 + 2 * m));
+  const int p = index_below(wa.w[0], n);
+  const int q = pick_partner(K, c, step, call, k, m, wa, wb, p, n);
+  PairRec<R> r;
+  r.pq = (unsigned)(cs + p) | (unsigned)(cs + q) << 16;
+  r.info = (unsigned)ci << 16 | (unsigned)np << 8 | (unsigned)m;
+  r.u = unif_r<R>(wa.w[2]);
+  R seps, ceps;  // eps = 2 pi U_eps, as sin(pi 2 U) and cos(pi 2 U)
+  sincospi_r((R)2.0 * unif_r<R>(wa.w[3]), &seps, &ceps);
+  const R cchi = cos_chi<R, false>(K, unif_r<R>(wb.w[0]));  // eq. chi_iso
+  const R schi = sqrt(fmax((R)0.0, ((R)1.0 - cchi) * ((R)1.0 + cchi)));
+  r.n[0] = ceps * schi;  // eq. n
+  r.n[1] = seps * schi;
+  r.n[2] = cchi;
+  return r;
+}
+
+// The outcome whose first pair is `first` (pair r0 of those held; rec(r) gives
+// the later ones): the arithmetic of ntc_outcome_small on drawn pairs.  The
+// velocities it changes stay in the entries of its pairs and end as changes;
+// entries it does not fill are marked.
+template <int SIG, class R, int PAIRS, class Rec>
+__device__ __attribute__((always_inline)) inline void apply_outcome(const SimConst& K, const PairRec<R>& first, int r0, Rec rec,
+                                     const R* v0, int st, PairLds<R, PAIRS>& P, int& acc,
+                                     int& gmx) {
+  const R gmax = (R)K.g_max;
+  const int np = (int)(first.info >> 8 & 0xffu), e0 = 2 * r0;
+  int cnt = 0;
+  PairRec<R> c = first;
+  for (int m = 0; m < np; ++m) {
+    if (m > 0) c = rec(r0 + m);
+    const int p = (int)(c.pq & 0xffffu), q = (int)(c.pq >> 16);
+    int ip = -1, iq = -1;
+    for (int t = 0; t < cnt; ++t) {
+      const int s = P.slot[e0 + t];
+      if (s == p) ip = t;
+      if (s == q) iq = t;
+    }
+    R up[3], uq[3];
+    for (int d = 0; d < 3; ++d) {
+      up[d] = ip >= 0 ? P.dv[d][e0 + ip] : v0[d * st + p];
+      uq[d] = iq >= 0 ? P.dv[d][e0 + iq] : v0[d * st + q];
+    }
+    const R dx = up[0] - uq[0], dy = up[1] - uq[1], dz = up[2] - uq[2];
+    const R g = sqrt(dx * dx + dy * dy + dz * dz);
+    if (g > gmax) ++gmx;
+    if (c.u < accept_ratio<SIG, R>(K, g)) {
+      ++acc;
+      if (ip < 0) {
+        ip = cnt++;
+        P.slot[e0 + ip] = (unsigned short)p;
+      }
+      if (iq < 0) {
+        iq = cnt++;
+        P.slot[e0 + iq] = (unsigned short)q;
+      }
+      R pn[3], qn[3];
+      post_collision<R, false>(K, up, uq, g, c.n, (R)0.0, pn, qn);
+      for (int d = 0; d < 3; ++d) {
+        P.dv[d][e0 + ip] = pn[d];
+        P.dv[d][e0 + iq] = qn[d];
+      }
+    }
+  }
+  for (int t = 0; t < 2 * np; ++t) {
+    if (t >= cnt) {
+      P.slot[e0 + t] = (unsigned short)kNoSlot;
+      continue;
+    }
+    for (int d = 0; d < 3; ++d)
+      P.dv[d][e0 + t] = P.dv[d][e0 + t] - v0[d * st + P.slot[e0 + t]];
+  }
+}
+
+// Pair r, its info and its neighbours' (~0 for none): the ends of its cell's pairs.
+__device__ inline void mark_cell_range(CellRanges& cr, int r, unsigned info, unsigned before,
+                                       unsigned after) {
+  const unsigned ci = info >> 16;
+  if (ci >= (unsigned)kCellCache) return;
+  if ((before >> 16) != ci) cr.lo[ci] = (short)r;
+  if ((after >> 16) != ci) cr.hi[ci] = (short)(r + 1);
+}
+
+// Adds to D the changes of tile slot j (of the tile's cell ci) among the nr pairs
+// held, in pair order: increasing outcome, the order of eq. avg_outcome.
+template <class R, int PAIRS>
+__device__ inline void slot_changes(const PairLds<R, PAIRS>& P, const CellRanges& cr, int nr, int ci,
+                                    int j, R D[3]) {
+  const bool ranged = ci < kCellCache;
+  const int lo = ranged ? cr.lo[ci] : 0, hi = ranged ? cr.hi[ci] : nr;
+  constexpr int W = 4;  // pairs looked at together (their loads do not wait for each other)
+  for (int r = lo; r < hi; r += W) {
+    unsigned s[W], hit = 0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) s[i] = P.slot2[r + i < hi ? r + i : hi - 1];
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+      if (r + i < hi)
+        hit |= ((s[i] & 0xffffu) == (unsigned)j ? 1u << (2 * i) : 0u) |
+               ((s[i] >> 16) == (unsigned)j ? 2u << (2 * i) : 0u);
+    for (; hit; hit &= hit - 1u) {
+      const int e = 2 * r + __ffsll((long long)hit) - 1;
+      for (int d = 0; d < 3; ++d) D[d] += P.dv[d][e];
+    }
+  }
+}
+
+// Whether tile_dense can run a call of this tile: at most kDenseMaxPairs pairs
+// per outcome.  Leaves the most pairs any of them can have in L.smax (uniform).
+template <class R>
+__device__ inline bool dense_fits(const SimConst& K, const PartArgs& a, int c0, int ncells,
+                                  DenseLds<R>& L) {
+  if (threadIdx.x == 0) L.smax = 0;
+  __syncthreads();
+  int most = 0;
+  for (int ci = threadIdx.x; ci < ncells; ci += kTileThreads) {
+    const int n = a.cstart[c0 + ci + 1] - a.cstart[c0 + ci];
+    const double x = (double)n * (double)(n - 1) * K.pmax / 2.0 + (1.0 - 0x1.0p-53);
+    const int s = n < 2 ? 0 : (x < (double)kDenseMaxPairs + 1.0 ? (int)floor(x) : kDenseMaxPairs + 1);
+    most = s > most ? s : most;
+  }
+  for (int w = 0; w < kTileThreads / 64; ++w) {  // one wave after another
+    if ((int)(threadIdx.x >> 6) == w) {
+      for (int off = 32; off > 0; off >>= 1) {
+        const int o = __shfl_xor(most, off);
+        most = o > most ? o : most;
+      }
+      if ((threadIdx.x & 63) == 0 && most > L.smax) L.smax = most;
+    }
+    __syncthreads();
+  }
+  return L.smax <= kDenseMaxPairs && ncells < 0x8000;
+}
+
+// One collision call over a tile held in LDS (8^3 cells, 10,240 particles, 1.8 pairs
+// per outcome, 32 outcomes: 0.35 ms a pass; with event lists 2 ms), its pairs drawn one per thread and
+// applied one outcome per thread, in chunks: N_pairs of 256 (cell, four outcomes)
+// items at a time, their pairs numbered by a scan in (cell, outcome) order, then
+// up to 256 pairs at a time, an outcome whole in the chunk that its first pair's
+// number falls into.  D (zeroed by the caller before a barrier) receives N_avg
+// <dv> in the order of eq. avg_outcome, as tile_run leaves it.
+template <int SIG, class R>
+__device__ __attribute__((always_inline)) inline void tile_dense(const SimConst& K, const PartArgs& a, int call, int64_t step,
+                                  int c0, int ncells, int s0, int ns, const R* v0, R* D,
+                                  const int* cell_of, int st, DenseLds<R>& L) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int navg = K.navg, ngroups = (navg + 3) >> 2;
+  const int64_t items = (int64_t)ncells * ngroups;
+  const int smax = L.smax > 0 ? L.smax : 1;
+  const int C = kDenseChunk - (smax - 1);  // first pairs' numbers of a chunk
+  if (tid == 0) L.accepted = L.over_gmax = 0;
+  for (int64_t ib = 0; ib < items; ib += kTileThreads) {
+    const int64_t item = ib + tid;
+    int ci = 0, k0 = 0, cnt = 0, np[4] = {0, 0, 0, 0};
+    if (item < items) {
+      ci = (int)(item / ngroups);
+      k0 = 4 * (int)(item - (int64_t)ci * ngroups);
+      const int n = a.cstart[c0 + ci + 1] - a.cstart[c0 + ci];
+      if (n >= 2) {
+        const U64x4 w = npairs_block(K, c0 + ci, step, call, k0 >> 2);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+          if (k0 + kk < navg) np[kk] = (int)npairs_from(K, n, w.w[kk], a.flags);
+        cnt = np[0] + np[1] + np[2] + np[3];
+      }
+    }
+    // numbers of the item's pairs: exclusive scan over the workgroup
+    int incl = cnt;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl(incl, lane >= off ? lane - off : lane);
+      if (lane >= off) incl += o;
+    }
+    if (lane == 63) L.wsum[wave] = incl;
+    __syncthreads();
+    int start = incl - cnt, total = 0;
+    for (int w = 0; w < kTileThreads / 64; ++w) {
+      if (w < wave) start += L.wsum[w];
+      total += L.wsum[w];
+    }
+    for (int base = 0; base < total; base += C) {
+      L.rec[tid].info = ~0u;  // (no pair)
+      if (tid < kCellCache) L.cr.lo[tid] = L.cr.hi[tid] = 0;
+      __syncthreads();
+      int at = start;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        if (at >= base && at < base + C)
+          for (int m = 0; m < np[kk]; ++m) {
+            L.rec[at - base + m].info = (unsigned)ci << 16 | (unsigned)np[kk] << 8 | (unsigned)m;
+            L.rec[at - base + m].pq = (unsigned)(k0 + kk);
+          }
+        at += np[kk];
+      }
+      __syncthreads();
+      const unsigned info = L.rec[tid].info;
+      const bool pair = info != ~0u;
+      PairRec<R> r{};
+      if (pair) {
+        const int pci = (int)(info >> 16), c = c0 + pci;
+        const int cs = a.cstart[c];
+        r = draw_pair<R>(K, c, pci, cs - s0, a.cstart[c + 1] - cs, step, call, (int)L.rec[tid].pq,
+                         (int)(info & 0xffu), (int)(info >> 8 & 0xffu));
+        mark_cell_range(L.cr, tid, info, tid > 0 ? L.rec[tid - 1].info : ~0u,
+                        tid + 1 < kDenseChunk ? L.rec[tid + 1].info : ~0u);
+      } else {
+        L.P.slot[2 * tid] = L.P.slot[2 * tid + 1] = (unsigned short)kNoSlot;
+      }
+      __syncthreads();  // every thread has its record's cell and outcome
+      if (pair) L.rec[tid] = r;
+      __syncthreads();
+      if (pair && (info & 0xffu) == 0u) {
+        int acc = 0, gmx = 0;
+        apply_outcome<SIG, R>(K, r, tid, [&](int i) { return L.rec[i]; }, v0, st, L.P, acc, gmx);
+        if (acc) atomicAdd(&L.accepted, acc);
+        if (gmx) atomicAdd(&L.over_gmax, gmx);
+      }
+      __syncthreads();
+      for (int j = tid; j < ns; j += kTileThreads) {
+        R d[3] = {D[j], D[st + j], D[2 * st + j]};
+        slot_changes(L.P, L.cr, kDenseChunk, cell_of[j] - c0, j, d);
+        for (int q = 0; q < 3; ++q) D[q * st + j] = d[q];
+      }
+      __syncthreads();  // the chunk's changes are consumed
+    }
+    __syncthreads();  // the scan's sums are consumed
+  }
+  if (tid == 0)
+    count_pairs(a, (unsigned long long)L.accepted, (unsigned long long)L.over_gmax);
+  __syncthreads();
+}
+
 // The outcomes of one cell that have candidate pairs, in increasing outcome
 // order, summed into D (eq. avg_outcome; the division by N_avg is done where D
 // is read).  Outcomes already run by a lane contribute their stored changes;
@@ -584,8 +889,7 @@ __device__ __attribute__((always_inline)) inline void tile_run(const SimConst& K
     cell_outcomes<SIG, R, FULL, LANE_ONLY, SORT>(K, a, call, step, c, ci, cs, n, v0, u, D, mark, tl, tagbase,
                                            st, stu, L, li, ne, first, all, acc, gmx);
   }
-  if (acc) atomicAdd(&a.counters[kCntAccepted], acc);
-  if (gmx) atomicAdd(&a.counters[kCntGmax], gmx);
+  count_pairs(a, acc, gmx);
   __syncthreads();
 }
 
@@ -765,7 +1069,7 @@ __device__ inline void half_kick_f64(const SimConst& K, const double acc[3], dou
   double coll[3] = {0.0, 0.0, 0.0};
   if (K.collisions) {
     double I[3] = {0.0, 0.0, 0.0};
-    double coef = (K.w * K.dt * (double)(n - 1)) / (2.0 * K.dV);
+    double coef = K.src_half * (double)(n - 1);
     if (n >= 2) source_integral_t<SIG>(K, v, t_src, I);
     for (int d = 0; d < 3; ++d) coll[d] = D[d] - ((n >= 2) ? coef * I[d] : 0.0);
   }
@@ -815,26 +1119,85 @@ __global__ void __launch_bounds__(kBlock) k_paper_drift_f64(SimConst K, PartArgs
   }
 }
 
-// Registers are capped for four resident waves per SIMD (128 VGPRs), accepting
-// a few spills: the pass is latency bound and gains more from resident waves
-// than it loses to spill traffic.  The paper family's instances take the same
-// cap: their drift term's root solves run before the pass (k_paper_drift_f64).
-template <int FAM, int SIG, bool FULL, bool FAST>
-__global__ void __launch_bounds__(kTileThreads, FAST ? PIC_F64_LEAN_WAVES : PIC_F64_WAVES)
+// The numbers of tile b's drawn pairs (call B, call A; 0 for a call that the pass
+// does not run).
+__device__ inline void tile_records(const PartArgs& a, int b, bool coll, int n[2]) {
+  n[0] = coll && (a.mode & kDoB) ? a.nrec[2 * b] : 0;
+  n[1] = coll && (a.mode & (kDoA | kCollideOnly)) ? a.nrec[2 * b + 1] : 0;
+}
+
+// The collision part of a pass's LDS: the event lists of both calls drawn in the
+// tile, a chunk of tile_dense, or the changes of the pairs drawn before the pass.
+template <class R, class Lists, int PAIRS>
+struct PassLds {
+  Lists cl;
+  __device__ Lists& lists() { return cl; }
+};
+template <class R, class Lists>
+struct PassLds<R, Lists, kPairsChunks> {
+  DenseLds<R> chunk;
+  __device__ int& lists() { return chunk.smax; }  // (no event lists)
+};
+template <class R, class Lists>
+struct PassLds<R, Lists, kPairsDrawn> {
+  PairLds<R, kRecCap> P;  // the call that runs
+  CellRanges cr[2];       // of call B and call A
+  __device__ CellRanges& lists() { return cr[0]; }  // (no event lists)
+  // before the tile's first barrier
+  __device__ void clear_ranges() {
+    for (int i = threadIdx.x; i < 2 * kCellCache; i += kTileThreads) {
+      CellRanges& c = cr[i / kCellCache];
+      c.lo[i % kCellCache] = c.hi[i % kCellCache] = 0;
+    }
+  }
+  // This thread's pair of call li (n pairs), loaded ahead of its use; the ends of
+  // the cells' pairs.
+  __device__ void load(int li, const PairRec<R>* list, int n, PairRec<R>& mine) {
+    const int r = threadIdx.x;
+    if (r >= n) return;
+    mine = list[r];
+    mark_cell_range(cr[li], r, mine.info, r > 0 ? list[r - 1].info : ~0u,
+                    r + 1 < n ? list[r + 1].info : ~0u);
+  }
+  // The call on v0: one outcome per thread (its first pair's); then a barrier.
+  template <int SIG>
+  __device__ __attribute__((always_inline)) void apply(const SimConst& K, const PartArgs& a,
+                                                       const PairRec<R>* list, int n,
+                                                       const PairRec<R>& mine, const R* v0, int st) {
+    if ((int)threadIdx.x < n && (mine.info & 0xffu) == 0u) {
+      int acc = 0, gmx = 0;
+      apply_outcome<SIG, R>(K, mine, (int)threadIdx.x, [&](int i) { return list[i]; }, v0, st, P, acc,
+                            gmx);
+      count_pairs(a, (unsigned long long)acc, (unsigned long long)gmx);
+    }
+    __syncthreads();
+  }
+};
+
+// Registers are capped for four resident waves per SIMD (128 VGPRs, no spills with
+// the pairs drawn before the pass; ten spilled registers made it slower than three
+// waves, 50 at five waves cost 40 %), three in the paper family, whose source
+// needs more; its drift term's root solves run before the pass (k_paper_drift_f64).
+template <int FAM, int SIG, bool FULL, bool FAST, int PAIRS = kPairsInTile>
+__global__ void __launch_bounds__(kTileThreads, PAIRS == kPairsDrawn    ? (FAM == 0 ? PIC_F64_REC_PAPER_WAVES : PIC_F64_REC_WAVES)
+                                                : PAIRS == kPairsChunks ? PIC_F64_DENSE_WAVES
+                                                : FAST                  ? PIC_F64_LEAN_WAVES
+                                                                        : PIC_F64_WAVES)
     k_particles_f64(SimConst K, PartArgs a) {
+  constexpr bool REC = PAIRS == kPairsDrawn, DENSE = PAIRS == kPairsChunks;
+  static_assert(PAIRS == kPairsInTile || FAST, "these take the tiles they can and leave the others");
   a = member_view(K, a);
   if (a.step_dev) {  // a captured step: its step index from the device
     a.nb = *K.stepc;
     a.na = a.nb + 1;
   }
   // the copy-on-write scratch of outcomes run by a cell thread is global
-  __shared__ double lv0[3 * kLdsSlots], lD[3 * kLdsSlots], lacc[3 * kLdsSlots];
+  __shared__ double lv0[3 * kLdsSlots], lD[REC ? 1 : 3 * kLdsSlots], lacc[3 * kLdsSlots];
   __shared__ int lkey[kLdsSlots];
   __shared__ int lcs[kCellCache + 1];  // cell starts of a tile of at most kCellCache cells
-  // (one pool size for both instances: a larger one in the general instance
-  // cut its occupancy more than it gained)
-  __shared__ CollideLds<double, 2, 128> cl;  // both calls of the pass drawn up front
-  __shared__ int sh_i[4];
+  __shared__ PassLds<double, CollideLds<double, 2, 128>, PAIRS> cu;
+  auto& cl = cu.lists();
+  __shared__ int sh_i[6];
   const int tid = threadIdx.x;
   const int NP = (int)K.np;
   auto tile = [&](const int b) __attribute__((always_inline)) {
@@ -843,16 +1206,24 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_F64_LEAN_WAVES : PIC_
       sh_i[1] = min(a.tile_c0[b + 1], K.nn);
       sh_i[2] = a.tile_s0[b];
       sh_i[3] = a.tile_s0[b + 1];
-      tile_lists_clear(cl);
+      if constexpr (REC) tile_records(a, b, K.collisions || (a.mode & kCollideOnly), sh_i + 4);
+      else if constexpr (!DENSE) tile_lists_clear(cl);
     }
+    if constexpr (REC) cu.clear_ranges();
     __syncthreads();
     const int c0 = sh_i[0], ncells = max(sh_i[1] - sh_i[0], 0), s0 = sh_i[2], ns = sh_i[3] - sh_i[2];
     if (ns <= 0) return;
-    if (FAST && ns > kLdsSlots) {  // (uniform) the general instance takes this tile
-      defer_tile(a, b);
+    const bool coll = K.collisions || (a.mode & kCollideOnly);
+    if (FAST && (ns > kLdsSlots || (REC && coll && min(sh_i[4], sh_i[5]) < 0))) {
+      defer_tile(a, b);  // (uniform) the general instance takes this tile
       return;
     }
     const bool lds = FAST || ns <= kLdsSlots;
+    if constexpr (DENSE)
+      if (coll && !dense_fits(K, a, c0, ncells, cu.chunk)) {
+        defer_tile(a, b);  // (uniform)
+        return;
+      }
     const int st = lds ? kLdsSlots : NP;
     double* v0 = lds ? lv0 : a.gv0 + s0;
     double* u = a.gu + s0;
@@ -860,9 +1231,11 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_F64_LEAN_WAVES : PIC_
     int* mark = a.gmark + s0;
     int* tl = a.gtl + s0;
     const double dt = K.dt;
-    const double inv_navg_den = (double)K.navg;
+    // (exact for a power-of-two N_avg: then the quotients by N_avg are products)
+    const double navg_d = (double)K.navg, inv_navg = 1.0 / navg_d;
+    const bool navg_pow2 = (K.navg & (K.navg - 1)) == 0;
+    auto over_navg = [&](double x) { return navg_pow2 ? x * inv_navg : x / navg_d; };
 
-    const bool pass_coll = K.collisions && !(a.mode & kCollideOnly);
     // A tile held in LDS computes the field part of its first kick while it
     // loads and keeps it in lacc; with both halves in one pass kick B (end of
     // step n) and kick A (start of step n + 1) are at the same time and
@@ -870,7 +1243,11 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_F64_LEAN_WAVES : PIC_
     const bool pre = lds && !(a.mode & kCollideOnly);
     const bool reuse_A = pre && (!(a.mode & kDoB) || a.na == a.nb + 1);
     const double t_pre = (a.mode & kDoB) ? ((double)a.nb + 1.0) * dt : (double)a.na * dt;
-    if (pass_coll) tile_zero_D(ns, st, D);
+    if (coll && !REC) tile_zero_D(ns, st, D);
+    PairRec<double> rec;  // REC: this thread's pair of the call that runs next
+    auto load_pairs = [&](int li, const void* list) {
+      if constexpr (REC) cu.load(li, (const PairRec<double>*)list + (int64_t)b * kRecCap, sh_i[4 + li], rec);
+    };
     for (int j = tid; j < ns; j += kTileThreads) {
       const int p = s0 + j;
       for (int d = 0; d < 3; ++d) v0[d * st + j] = a.v[(int64_t)d * NP + p];
@@ -888,30 +1265,64 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_F64_LEAN_WAVES : PIC_
     const bool few_cells = ncells <= kCellCache;
     if (few_cells)
       for (int i = tid; i <= ncells; i += kTileThreads) lcs[i] = a.cstart[c0 + i];
-    if (pass_coll) tile_draw_pass(K, a, c0, ncells, cl);
+    // (a pair's ten registers are not held across the gather)
+    if (REC && coll) load_pairs((a.mode & kDoB) ? 0 : 1, (a.mode & kDoB) ? a.recB : a.recA);
+    if constexpr (!REC && !DENSE)
+      if (coll && !(a.mode & kCollideOnly)) tile_draw_pass(K, a, c0, ncells, cl);
     __syncthreads();
+    // one call on v0: li (0 B, 1 A or the collide-only one)
+    auto run_call = [&](int li) __attribute__((always_inline)) {
+      const int call = li ? a.callA : a.callB;
+      const int64_t step = li ? a.na : a.nb;
+      if constexpr (REC) {
+        cu.template apply<SIG>(K, a, (const PairRec<double>*)(li ? a.recA : a.recB) + (int64_t)b * kRecCap,
+                               sh_i[4 + li], rec, v0, st);
+      } else if constexpr (DENSE) {
+        tile_dense<SIG, double>(K, a, call, step, c0, ncells, s0, ns, v0, D, lkey, st, cu.chunk);
+      } else {
+        if constexpr (!FAST) {
+          if (a.mode & kCollideOnly) {
+            tile_collide<SIG, double, FULL>(K, a, call, step, c0, ncells, s0, ns, v0, u, D, mark, tl, 0, st,
+                                            NP, cl);
+            return;
+          }
+        }
+        tile_run<SIG, double, FULL, FAST, true>(K, a, li, call, step, c0, ncells, s0, ns, v0, u, D, mark,
+                                                tl, li ? K.navg : 0, st, NP, cl,
+                                                few_cells ? lcs : nullptr);
+      }
+    };
+    // N_avg <dv> of slot j in call li
+    auto changes = [&](int li, int j, double Dj[3]) {
+      if constexpr (REC) {
+        Dj[0] = Dj[1] = Dj[2] = 0.0;
+        slot_changes(cu.P, cu.cr[li], sh_i[4 + li], lkey[j] - c0, j, Dj);
+      } else {
+        for (int d = 0; d < 3; ++d) Dj[d] = D[d * st + j];
+      }
+    };
     // cell and particle count of slot j at the start of the pass
     auto cell_of = [&](int j) { return lds ? lkey[j] : a.key[s0 + j]; };
     auto count_of = [&](int c) {
       return few_cells ? lcs[c - c0 + 1] - lcs[c - c0] : a.cstart[c + 1] - a.cstart[c];
     };
-    if (FAST && pass_coll &&
-        !tile_lane_only(cl, (a.mode & kDoB) ? 0 : 1, (a.mode & kDoA) ? 2 : 1)) {
-      defer_tile(a, b);  // (uniform, and nothing written to memory yet)
-      return;
-    }
+    if constexpr (FAST && !REC && !DENSE)
+      if (coll && !tile_lane_only(cl, (a.mode & kDoB) ? 0 : 1, (a.mode & kDoA) ? 2 : 1)) {
+        defer_tile(a, b);  // (uniform, and nothing written to memory yet)
+        return;
+      }
 
-    if (!FAST && (a.mode & kCollideOnly)) {  // (the lean instance never runs collide-only)
-      tile_collide<SIG, double, FULL>(K, a, a.callA, a.na, c0, ncells, s0, ns, v0, u, D, mark, tl, 0, st,
-                                NP, cl);
+    if constexpr (!FAST || REC || DENSE) if (a.mode & kCollideOnly) {
+      run_call(1);
       for (int j = tid; j < ns; j += kTileThreads) {
         int c = a.key[s0 + j];
         int n = a.cstart[c + 1] - a.cstart[c];
-        double vp[3] = {v0[j], v0[st + j], v0[2 * st + j]}, I[3] = {0, 0, 0};
-        double coef = (K.w * K.dt * (double)(n - 1)) / (2.0 * K.dV);
+        double vp[3] = {v0[j], v0[st + j], v0[2 * st + j]}, I[3] = {0, 0, 0}, Dj[3];
+        double coef = K.src_half * (double)(n - 1);
         if (n >= 2) source_integral_t<SIG>(K, vp, a.tB, I);
+        changes(1, j, Dj);
         for (int d = 0; d < 3; ++d) {
-          a.Dout[(int64_t)d * NP + s0 + j] = D[d * st + j] / inv_navg_den;
+          a.Dout[(int64_t)d * NP + s0 + j] = over_navg(Dj[d]);
           a.Sout[(int64_t)d * NP + s0 + j] = (n >= 2) ? coef * I[d] : 0.0;
         }
       }
@@ -925,9 +1336,7 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_F64_LEAN_WAVES : PIC_
     if (a.mode & kDoB) {
       // collision call B at t^{nb+1/2} on v^{nb+1/2}, then the second half kick at t^{nb+1}
       const double th = ((double)a.nb + 0.5) * dt, t1 = ((double)a.nb + 1.0) * dt;
-      if (K.collisions)
-        tile_run<SIG, double, FULL, FAST, true>(K, a, 0, a.callB, a.nb, c0, ncells, s0, ns, v0, u, D, mark, tl, 0, st,
-                                  NP, cl, few_cells ? lcs : nullptr);
+      if (coll) run_call(0);
       for (int j = tid; j < ns; j += kTileThreads) {
         int p = s0 + j;
         double acc[3];
@@ -943,15 +1352,19 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_F64_LEAN_WAVES : PIC_
         double vp[3] = {v0[j], v0[st + j], v0[2 * st + j]};
         double aa[3] = {a.ash[p], a.ash[NP + p], a.ash[2 * NP + p]};
         double Dj[3] = {0.0, 0.0, 0.0};
-        if (K.collisions)
+        if (K.collisions) {
+          changes(0, j, Dj);
           for (int d = 0; d < 3; ++d) {
-            Dj[d] = D[d * st + j] / inv_navg_den;
-            D[d * st + j] = 0.0;  // cleared for call A (the barrier below orders it)
+            Dj[d] = over_navg(Dj[d]);
+            if (!REC) D[d * st + j] = 0.0;  // cleared for call A (the barrier below orders it)
           }
+        }
         half_kick_f64<FAM, SIG>(K, acc, t1, th, t1, th, aa, n, Dj, vp);
         for (int d = 0; d < 3; ++d) v0[d * st + j] = vp[d];
       }
-      if (tid == 0) cl.pool_n = 0;
+      if (REC && coll && (a.mode & kDoA)) load_pairs(1, a.recA);
+      if constexpr (!REC && !DENSE)
+        if (tid == 0) cl.pool_n = 0;
       __syncthreads();
       if (!(a.mode & kDoA)) {
         for (int j = tid; j < ns; j += kTileThreads)
@@ -962,9 +1375,7 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_F64_LEAN_WAVES : PIC_
 
     // collision call A at t^{na} on v^{na}, first half kick, drift to t^{na+1}
     const double t0 = (double)a.na * dt, th = ((double)a.na + 0.5) * dt, t1 = ((double)a.na + 1.0) * dt;
-    if (K.collisions)
-      tile_run<SIG, double, FULL, FAST, true>(K, a, 1, a.callA, a.na, c0, ncells, s0, ns, v0, u, D, mark, tl, K.navg,
-                                st, NP, cl, few_cells ? lcs : nullptr);
+    if (coll) run_call(1);
     for (int base = 0; base < ns; base += kTileThreads) {
       int j = base + tid;
       bool valid = j < ns;
@@ -984,8 +1395,10 @@ __global__ void __launch_bounds__(kTileThreads, FAST ? PIC_F64_LEAN_WAVES : PIC_
         double vp[3] = {v0[j], v0[st + j], v0[2 * st + j]};
         double aa[3] = {a.ash[p], a.ash[NP + p], a.ash[2 * NP + p]};
         double Dj[3] = {0.0, 0.0, 0.0};
-        if (K.collisions)
-          for (int d = 0; d < 3; ++d) Dj[d] = D[d * st + j] / inv_navg_den;
+        if (K.collisions) {
+          changes(1, j, Dj);
+          for (int d = 0; d < 3; ++d) Dj[d] = over_navg(Dj[d]);
+        }
         half_kick_f64<FAM, SIG>(K, acc, t0, t0, th, t0, aa, n, Dj, vp);
         // drift (eq. velocity_verlet) with the manufactured term
         double vm[3], vdm[3], h[3] = {0.0, 0.0, 0.0};
