@@ -1060,12 +1060,15 @@ int errors_into(pic_ctx* c, pic_error_norms* out, double* epart, double* npart, 
   double t = (double)c->step * K.dt;
   const int nbp = err_grid(K.np), nbn = err_grid(K.nn);
   int s = c->cur;
-  if (c->precision == PIC_FP64)
-    k_err_particles_f64<<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->x[s], c->v[s], c->id[s], epart,
-                                                       c->flags);
-  else
-    k_err_particles_mixed<<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->key, c->off[s], c->vf[s],
-                                                         c->id[s], epart, c->flags);
+  if (c->precision == PIC_FP64) {
+    k_err_particles_f64<<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->x[s], c->v[s], c->sh[s],
+                                                             c->id[s], epart, c->flags);
+  } else {
+    k_err_positions_mixed<<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->key, c->off[s], c->id[s],
+                                                               epart, c->flags);
+    (K.family == 1 ? k_err_velocities_mixed<true> : k_err_velocities_mixed<false>)
+        <<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->vf[s], c->id[s], epart, c->flags);
+  }
   k_err_nodes<<<G(c, nbn), kBlock, 0, c->stream>>>(K, t, c->phi, npart);
   k_err_final<<<G(c, 1), kBlock, 0, c->stream>>>(K, epart, nbp, npart, nbn, norms);
   LAUNCH_CHECK(c, "errors");

@@ -159,22 +159,35 @@ __device__ inline int index_below(uint64_t w, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// Safeguarded Newton for a monotone CDF on [lo, hi].
+// Safeguarded Halley iteration for a monotone CDF on [lo, hi]: F(x, dens, slope)
+// gives F, its density and the density's slope, which the CDFs here have at no
+// further cost, and the order three saves about half of Newton's evaluations.
+// F.done(x, step): whether the root is reached after a step of that length (the
+// next one, about the cube of this one in the CDF's own length, would be below
+// the rounding of x).
 // ---------------------------------------------------------------------------
 template <class Cdf>
-__device__ double invert_cdf(const Cdf& F, double target, double lo, double hi, double x) {
+__device__ inline double invert_cdf(const Cdf& F, double target, double lo, double hi, double x) {
   if (!(x > lo && x < hi)) x = 0.5 * (lo + hi);
   for (int it = 0; it < 200; ++it) {
-    double dens;
-    double res = F(x, dens) - target;
+    double dens, slope;
+    const double res = F(x, dens, slope) - target;
     if (res == 0.0) break;
     if (res > 0.0) hi = x; else lo = x;
-    double nx = x - res / dens;
-    if (!(dens > 0.0) || !(nx > lo && nx < hi)) nx = 0.5 * (lo + hi);
-    if (nx == lo || nx == hi) { x = nx; break; }
-    double step = fabs(nx - x);
+    const double den = 2.0 * dens * dens - res * slope;
+    double nx = x - 2.0 * res * dens / den;
+    const bool halley = dens > 0.0 && den > 0.0;
+    // (before the bracket's test: at the root the step is rounding, to either side)
+    if (halley && F.done(x, fabs(nx - x))) {
+      x = fmin(fmax(nx, lo), hi);
+      break;
+    }
+    if (!(halley && nx > lo && nx < hi)) nx = 0.5 * (lo + hi);
+    if (nx == lo || nx == hi || fabs(nx - x) <= 4.440892098500626e-16 * fabs(nx)) {
+      x = nx;
+      break;
+    }
     x = nx;
-    if (step <= 4.440892098500626e-16 * fabs(x)) break;
   }
   return x;
 }
@@ -182,65 +195,69 @@ __device__ double invert_cdf(const Cdf& F, double target, double lo, double hi, 
 // ---------------------------------------------------------------------------
 // Manufactured solution.
 // ---------------------------------------------------------------------------
-// Sec. 5.2 position densities per unit length and their CDFs from 0.
-struct PaperPosCdf {
-  int d;
-  double L, e;  // e = exp(t / T)
-  __device__ double operator()(double x, double& dens) const {
-    double s = x / L;
-    if (d == 0) {
-      dens = (1.0 + 0.2 * e * sinpi(2.0 * s)) / L;
-      return s + 0.2 * e * (1.0 - cospi(2.0 * s)) / (2.0 * kPi);
-    }
-    if (d == 1) {
-      double c = 0.15 * e;
-      dens = (1.0 + 0.2 * sinpi(2.0 * (s - c))) / L;
-      return s + (cospi(2.0 * c) - cospi(2.0 * (s - c))) / (10.0 * kPi);
-    }
-    double c = e / 15.0;
-    dens = (1.0 - (e / 6.0) * sinpi(2.0 * (s + c))) / L;
-    return s - (e / (12.0 * kPi)) * (cospi(2.0 * c) - cospi(2.0 * (s + c)));
-  }
+// What the Sec. 5.2 positions need of the time: e = exp(t / T), the phase
+// shifts of y and z, and the trigonometric functions of those.
+struct PaperTime {
+  double e, sy, sz;              // shifts 0.15 e and e / 15
+  double sin_y, cos_y, sin_z, cos_z;  // of 2 pi times the shifts
 };
-
-// dF/dt at fixed x for the Sec. 5.2 position CDFs.
-__device__ inline double paper_dFdt(int d, double x, double L, double T, double e) {
-  double s = x / L;
-  if (d == 0) return (0.2 * e / T) * (1.0 - cospi(2.0 * s)) / (2.0 * kPi);
-  if (d == 1) {
-    double c = 0.15 * e, cdot = c / T;
-    return -(cdot / 5.0) * (sinpi(2.0 * c) + sinpi(2.0 * (s - c)));
-  }
-  double c = e / 15.0, cdot = c / T;
-  double br = cospi(2.0 * c) - cospi(2.0 * (s + c));
-  double dbr = 2.0 * kPi * cdot * (sinpi(2.0 * (s + c)) - sinpi(2.0 * c));
-  return -(e / (12.0 * kPi * T)) * br - (e / (12.0 * kPi)) * dbr;
+__device__ inline PaperTime paper_time(const SimConst& K, double t) {
+  PaperTime P{};
+  if (K.family == 1) return P;
+  P.e = exp(t / K.T);
+  P.sy = 0.15 * P.e;
+  P.sz = P.e / 15.0;
+  sincospi(2.0 * P.sy, &P.sin_y, &P.cos_y);
+  sincospi(2.0 * P.sz, &P.sin_z, &P.cos_z);
+  return P;
 }
+
+// Sec. 5.2 position densities per unit length and their CDFs from 0, as functions
+// of s = x / L: density (1 + amp sin 2 pi (s + shift)) / L, CDF s + amp (c0 -
+// cos 2 pi (s + shift)) / (2 pi).
+struct PaperPosCdf {
+  double inv_L, amp, shift, c0;
+  __device__ PaperPosCdf(const SimConst& K, const PaperTime& P, int d)
+      : inv_L(K.inv_L[d]),
+        amp(d == 0 ? 0.2 * P.e : (d == 1 ? 0.2 : -(P.e / 6.0))),
+        shift(d == 0 ? 0.0 : (d == 1 ? -P.sy : P.sz)),
+        c0(d == 0 ? 1.0 : (d == 1 ? P.cos_y : P.cos_z)) {}
+  __device__ double operator()(double x, double& dens, double& slope) const {
+    const double s = x * inv_L;
+    double sn, cs;
+    sincospi(2.0 * (s + shift), &sn, &cs);
+    dens = (1.0 + amp * sn) * inv_L;
+    slope = 2.0 * kPi * amp * cs * inv_L * inv_L;
+    return s + amp * (c0 - cs) * (0.5 / kPi);
+  }
+  // (the iteration's error grows by (2 pi)^2 times the cube of the step at most)
+  __device__ bool done(double, double step) const { return step * inv_L <= 1e-6; }
+};
 
 // Configuration family: CDF of z given (x, y), a = A sin(2 pi x/L) sin(2 pi y/L).
 struct CfgZCdf {
-  double L, a;
-  __device__ double operator()(double z, double& dens) const {
-    double s = z / L;
-    dens = (1.0 + a * sinpi(2.0 * s)) / L;
-    return s + a * (1.0 - cospi(2.0 * s)) / (2.0 * kPi);
+  double inv_L, a;
+  __device__ double operator()(double z, double& dens, double& slope) const {
+    const double s = z * inv_L;
+    double sn, cs;
+    sincospi(2.0 * s, &sn, &cs);
+    dens = (1.0 + a * sn) * inv_L;
+    slope = 2.0 * kPi * a * cs * inv_L * inv_L;
+    return s + a * (1.0 - cs) * (0.5 / kPi);
   }
+  __device__ bool done(double, double step) const { return step * inv_L <= 1e-6; }
 };
 
-// Paper velocity CDF in units of vhat: G(a) = (1 + erf a)/2 - a e^{-a^2}/sqrt(pi).
+// Paper velocity CDF in units of vhat on the lower half (a < 0):
+// G(a) = erfc(-a)/2 - a e^{-a^2}/sqrt(pi).
 struct PaperGCdf {
-  __device__ double operator()(double a, double& dens) const {
-    double ea = exp(-a * a);
+  __device__ double operator()(double a, double& dens, double& slope) const {
+    const double ea = exp(-a * a);
     dens = 1.1283791670955126 * a * a * ea;  // 2/sqrt(pi)
+    slope = 2.2567583341910251 * a * (1.0 - a * a) * ea;
     return 0.5 + 0.5 * erf(a) - 0.5641895835477563 * a * ea;
   }
-};
-
-struct NormalCdf {
-  __device__ double operator()(double z, double& dens) const {
-    dens = 0.3989422804014327 * exp(-0.5 * z * z);
-    return 0.5 * erfc(-0.7071067811865476 * z);
-  }
+  __device__ bool done(double a, double step) const { return step * (1.0 + a * a) <= 1e-6 * fabs(a); }
 };
 
 __device__ inline void init_uniforms(const SimConst& K, int64_t id, double xi[6]) {
@@ -280,7 +297,8 @@ __device__ inline void vhat_of_t(const SimConst& K, double t, double vh[3], doub
 // Standard normal quantile.  The root is taken on the lower tail, Phi(-z) =
 // min(xi, 1 - xi) (1 - xi is exact for xi >= 1/2), which keeps the residual
 // well conditioned in both tails; starting guess Abramowitz & Stegun 26.2.23
-// (|error| < 4.5e-4), then Newton steps on 0.5 erfc(-y / sqrt 2) in FP64.
+// (|error| < 4.5e-4), then Halley steps on 0.5 erfc(-y / sqrt 2) in FP64: one or
+// two, the next being below rounding once a step is under 1e-6 / (1 + y^2).
 __device__ inline double normal_quantile(double xi) {
   const double pp = xi < 0.5 ? xi : 1.0 - xi;
   const double t = sqrt(-2.0 * log(pp));
@@ -288,22 +306,34 @@ __device__ inline double normal_quantile(double xi) {
                        (1.0 + t * (1.432788 + t * (0.189269 + t * 0.001308))));
 #pragma unroll 1
   for (int it = 0; it < 4; ++it) {
-    double f = 0.5 * erfc(-0.7071067811865476 * y) - pp;
-    double dens = 0.3989422804014327 * exp(-0.5 * y * y);
-    double dy = f / dens;
+    const double f = 0.5 * erfc(-0.7071067811865476 * y) - pp;
+    const double dens = 0.3989422804014327 * exp(-0.5 * y * y);
+    const double dy = f / (dens + 0.5 * y * f);
     y -= dy;
-    if (fabs(dy) <= 1e-16 * fabs(y)) break;
+    if (fabs(dy) * (1.0 + y * y) <= 1e-6) break;
   }
   return xi < 0.5 ? y : -y;
 }
 
 // Paper family: a = G^{-1}(xi), time independent (v^M = vhat(t) a).  The
 // density of eq. fv is even, so G^{-1}(xi) = -G^{-1}(1 - xi): solve on the
-// lower half.
-__device__ __noinline__ double paper_a(double xi) {
+// lower half.  The guess is within 6 %: near the centre the inverted series
+// of G, in the tail G(a) ~ (|a| + 1/(2|a|)) e^{-a^2} / sqrt(pi) solved for the
+// exponent twice; one to three Halley steps follow.
+__device__ inline double paper_a(double xi) {
   const double pp = xi < 0.5 ? xi : 1.0 - xi;
-  double a0 = cbrt(2.6586807763582730 * (pp - 0.5));  // 1.5 sqrt(pi)
-  double a = invert_cdf(PaperGCdf{}, pp, -30.0, 0.0, a0);
+  double a;
+  if (pp > 0.2) {
+    a = cbrt(2.6586807763582730 * (pp - 0.5));  // 1.5 sqrt(pi)
+    const double b2 = a * a;
+    a = a * (1.0 + b2 * (0.2 + b2 * 0.0771));
+  } else {
+    double x = sqrt(-log(pp));
+    for (int it = 0; it < 2; ++it)
+      x = sqrt(fmax(0.3, -log(1.7724538509055159 * pp / (x + 0.5 / x))));
+    a = -x;
+  }
+  a = invert_cdf(PaperGCdf{}, pp, -30.0, 0.0, a);
   return xi < 0.5 ? a : -a;
 }
 
@@ -322,56 +352,68 @@ __device__ inline void manufactured_velocity(const SimConst& K, const double a[3
   }
 }
 
-__device__ inline void paper_position(const SimConst& K, const double xp[3], double t,
-                                             const double* guess, double x[3]) {
-  double e = exp(t / K.T);
-  for (int d = 0; d < 3; ++d) {
-    PaperPosCdf F{d, K.L[d], e};
-    x[d] = invert_cdf(F, xp[d], 0.0, K.L[d], guess ? guess[d] : K.L[d] * xp[d]);
-  }
+__device__ inline void paper_position(const SimConst& K, const double xp[3], const PaperTime& P,
+                                      const double* guess, double x[3]) {
+  for (int d = 0; d < 3; ++d)
+    x[d] = invert_cdf(PaperPosCdf(K, P, d), xp[d], 0.0, K.L[d], guess ? guess[d] : K.L[d] * xp[d]);
 }
 
 __device__ inline void cfg_position(const SimConst& K, const double xp[3], double x[3]) {
   x[0] = K.L[0] * xp[0];
   x[1] = K.L[1] * xp[1];
-  CfgZCdf F{K.L[2], K.rho_amp * sinpi(2.0 * x[0] / K.L[0]) * sinpi(2.0 * x[1] / K.L[1])};
+  CfgZCdf F{K.inv_L[2], K.rho_amp * sinpi(2.0 * xp[0]) * sinpi(2.0 * xp[1])};
   x[2] = invert_cdf(F, xp[2], 0.0, K.L[2], K.L[2] * xp[2]);
 }
 
-// eq. mms_sol for the positions; `guess` speeds up the paper-family roots.
-__device__ inline void manufactured_position(const SimConst& K, const double xp[3], double t,
+// eq. mms_sol for the positions at the time of P; `guess` speeds up the
+// paper-family roots.
+__device__ inline void manufactured_position(const SimConst& K, const double xp[3], const PaperTime& P,
                                              const double* guess, double x[3]) {
   if (K.family == 1) cfg_position(K, xp, x);
-  else paper_position(K, xp, t, guess, x);
+  else paper_position(K, xp, P, guess, x);
+}
+__device__ inline void manufactured_position(const SimConst& K, const double xp[3], double t,
+                                             const double* guess, double x[3]) {
+  manufactured_position(K, xp, paper_time(K, t), guess, x);
 }
 
-// xdot^M = -(dF/dt)/f at x^M (Sec. 3.2).
-__device__ inline void manufactured_xdot(const SimConst& K, const double xm[3], double t,
+// xdot^M = -(dF/dt)/f at x^M (Sec. 3.2), dF/dt at fixed x of the Sec. 5.2 CDFs:
+// amp and shift change by amp_t and shift_t, so 2 pi dF/dt = amp_t (c0 - cos) +
+// 2 pi amp shift_t (sin - s0), with sin and cos at x and c0, s0 at x = 0.
+__device__ inline void manufactured_xdot(const SimConst& K, const double xm[3], const PaperTime& P,
                                          double xd[3]) {
   if (K.family == 1) {
     xd[0] = xd[1] = xd[2] = 0.0;
     return;
   }
-  double e = exp(t / K.T);
+  const double rate = 1.0 / K.T;
+  const double amp_t[3] = {0.2 * P.e * rate, 0.0, -(P.e / 6.0) * rate};
+  const double shift_t[3] = {0.0, -P.sy * rate, P.sz * rate};
+  const double s0[3] = {0.0, -P.sin_y, P.sin_z};
   for (int d = 0; d < 3; ++d) {
-    PaperPosCdf F{d, K.L[d], e};
-    double dens;
-    (void)F(xm[d], dens);
-    xd[d] = -paper_dFdt(d, xm[d], K.L[d], K.T, e) / dens;
+    const PaperPosCdf F(K, P, d);
+    double sn, cs;
+    sincospi(2.0 * (xm[d] * F.inv_L + F.shift), &sn, &cs);
+    const double dens = (1.0 + F.amp * sn) * F.inv_L;
+    const double dFdt = amp_t[d] * (F.c0 - cs) * (0.5 / kPi) + F.amp * shift_t[d] * (sn - s0[d]);
+    xd[d] = -dFdt / dens;
   }
+}
+__device__ inline void manufactured_xdot(const SimConst& K, const double xm[3], double t,
+                                         double xd[3]) {
+  manufactured_xdot(K, xm, paper_time(K, t), xd);
 }
 
 // Number density f_x (eq. fx), integrating to N over the box.
-__device__ inline double number_density(const SimConst& K, const double x[3], double t) {
+__device__ inline double number_density(const SimConst& K, const double x[3], const PaperTime& P) {
   if (K.family == 1) {
     double s = sinpi(2.0 * x[0] / K.L[0]) * sinpi(2.0 * x[1] / K.L[1]) * sinpi(2.0 * x[2] / K.L[2]);
     return K.nphys / (K.L[0] * K.L[1] * K.L[2]) * (1.0 + K.rho_amp * s);
   }
-  double e = exp(t / K.T), r = K.nphys;
+  double r = K.nphys;
   for (int d = 0; d < 3; ++d) {
-    PaperPosCdf F{d, K.L[d], e};
-    double dens;
-    (void)F(x[d], dens);
+    double dens, slope;
+    (void)PaperPosCdf(K, P, d)(x[d], dens, slope);
     r *= dens;
   }
   return r;

@@ -511,10 +511,11 @@ __device__ inline void node_coords(const SimConst& K, int n, int& i, int& j, int
 // operator, through the Q1 mass weights (1, 4, 1) / 6 per axis (the consistent
 // mass matrix over the cell volume) for trilinear elements.
 __device__ inline double rhs_manufactured(const SimConst& K, int i, int j, int k, double t) {
+  const PaperTime P = paper_time(K, t);
   auto m_at = [&](int ii, int jj, int kk) {
     const double xn[3] = {ii * K.h[0], jj * K.h[1], kk * K.h[2]};
     double v = lap_phiM(K, xn, t);
-    if (K.p2f != 0.0) v += K.q * number_density(K, xn, t) / K.eps0;
+    if (K.p2f != 0.0) v += K.q * number_density(K, xn, P) / K.eps0;
     return v;
   };
   if (K.poisson_op != 1) return m_at(i, j, k);
@@ -1266,49 +1267,59 @@ __global__ void __launch_bounds__(kBlock) k_drift_f64(SimConst K, double t0, dou
 // ---------------------------------------------------------------------------
 constexpr int kErrBlocks = 1024;
 
+// One particle's position and velocity errors e against x^M, v^M into the sums
+// of a thread, and a block's sums into its row of part (component a0 on).
+__device__ inline void err_add(double e, double& s2, double& mx, bool& bad) {
+  bad |= !isfinite(e);
+  s2 += e * e;
+  mx = fmax(mx, fabs(e));
+}
+__device__ inline double wrapped_error(double ex, double L) {
+  if (ex >= 0.5 * L) ex -= L;
+  if (ex < -0.5 * L) ex += L;
+  return ex;
+}
+template <int N>
+__device__ inline void err_row(const double* s2, const double* mx, double* part, int a0, double* sh) {
+  for (int a = 0; a < N; ++a) {
+    const double s = block_sum(s2[a], sh);
+    const double m = block_max(mx[a], sh);
+    if (threadIdx.x == 0) {
+      part[blockIdx.x * 14 + a0 + a] = s;
+      part[blockIdx.x * 14 + 7 + a0 + a] = m;
+    }
+  }
+}
+
 __global__ void __launch_bounds__(kBlock) k_err_particles_f64(SimConst K, double t,
                                                               const double* x, const double* v,
-                                                              const int* id, double* part,
-                                                              int* flags) {
+                                                              const double* ash, const int* id,
+                                                              double* part, int* flags) {
   x = mem(K, x);
   v = mem(K, v);
+  ash = mem(K, ash);
   id = mem(K, id);
   part = mem(K, part);
   flags = mem(K, flags);
   __shared__ double sh[kWaves];
   double s2[6] = {0, 0, 0, 0, 0, 0}, mx[6] = {0, 0, 0, 0, 0, 0};
   bool bad = false;
+  const PaperTime P = paper_time(K, t);
   for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < K.np;
        i += (int64_t)gridDim.x * kBlock) {
-    double xq[3], xv[3], xm[3], a[3], vm[3], vd[3], e[6];
+    double xq[3], xm[3], vm[3], vd[3];
     position_uniforms(K, id[i], xq);
-    velocity_uniforms(K, id[i], xv);
-    double xp[3] = {x[i], x[K.np + i], x[2 * K.np + i]};
-    manufactured_position(K, xq, t, xp, xm);
-    velocity_shape(K, xv, a);
+    const double xp[3] = {x[i], x[K.np + i], x[2 * K.np + i]};
+    manufactured_position(K, xq, P, xp, xm);
+    const double a[3] = {ash[i], ash[K.np + i], ash[2 * K.np + i]};
     manufactured_velocity(K, a, t, vm, vd);
     for (int d = 0; d < 3; ++d) {
-      double ex = xp[d] - xm[d];
-      if (ex >= 0.5 * K.L[d]) ex -= K.L[d];
-      if (ex < -0.5 * K.L[d]) ex += K.L[d];
-      e[d] = ex;
-      e[3 + d] = v[d * K.np + i] - vm[d];
-    }
-    for (int a2 = 0; a2 < 6; ++a2) {
-      bad |= !isfinite(e[a2]);
-      s2[a2] += e[a2] * e[a2];
-      mx[a2] = fmax(mx[a2], fabs(e[a2]));
+      err_add(wrapped_error(xp[d] - xm[d], K.L[d]), s2[d], mx[d], bad);
+      err_add(v[d * K.np + i] - vm[d], s2[3 + d], mx[3 + d], bad);
     }
   }
   if (bad) atomicOr(&flags[kFlagNonFinite], 1);
-  for (int a2 = 0; a2 < 6; ++a2) {
-    double s = block_sum(s2[a2], sh);
-    double m = block_max(mx[a2], sh);
-    if (threadIdx.x == 0) {
-      part[blockIdx.x * 14 + a2] = s;
-      part[blockIdx.x * 14 + 7 + a2] = m;
-    }
-  }
+  err_row<6>(s2, mx, part, 0, sh);
 }
 
 __global__ void __launch_bounds__(kBlock) k_err_nodes(SimConst K, double t, const double* phi,

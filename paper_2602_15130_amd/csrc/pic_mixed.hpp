@@ -660,7 +660,7 @@ __global__ void __launch_bounds__(kTileThreads, PAIRS == kPairsDrawn    ? PIC_MI
 // particle's identity, that position and the time, so it runs before the pass
 // (which then keeps no root solver and its register budget); out is the idle
 // half of the double-buffered offsets.
-__global__ void __launch_bounds__(kBlock) k_paper_drift_mixed(SimConst K, PartArgs a, const float* off,
+__global__ void __launch_bounds__(kBlock, 4) k_paper_drift_mixed(SimConst K, PartArgs a, const float* off,
                                                               float* out) {
   a = member_view(K, a);
   off = mem(K, off);
@@ -670,8 +670,9 @@ __global__ void __launch_bounds__(kBlock) k_paper_drift_mixed(SimConst K, PartAr
     a.na = a.nb + 1;
   }
   const int64_t NP = K.np;
-  const double t0 = (double)a.na * K.dt, th = ((double)a.na + 0.5) * K.dt,
-               t1 = ((double)a.na + 1.0) * K.dt;
+  // (isolation mode: at both ends of the step, else at its middle)
+  const PaperTime Pa = paper_time(K, ((double)a.na + (K.isolate ? 0.0 : 0.5)) * K.dt);
+  const PaperTime Pb = paper_time(K, ((double)a.na + 1.0) * K.dt);
   for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < NP;
        p += (int64_t)gridDim.x * blockDim.x) {
     int cc[3];
@@ -681,13 +682,13 @@ __global__ void __launch_bounds__(kBlock) k_paper_drift_mixed(SimConst K, PartAr
     for (int d = 0; d < 3; ++d) xg[d] = ((double)cc[d] + (double)off[d * NP + p]) * K.h[d];
     if (K.isolate) {
       double xa[3], xb[3];
-      manufactured_position(K, xq, t0, xg, xa);
-      manufactured_position(K, xq, t1, xa, xb);
+      manufactured_position(K, xq, Pa, xg, xa);
+      manufactured_position(K, xq, Pb, xa, xb);
       for (int d = 0; d < 3; ++d) disp[d] = xb[d] - xa[d];
     } else {
       double xm[3], xd[3];
-      manufactured_position(K, xq, th, xg, xm);
-      manufactured_xdot(K, xm, th, xd);
+      manufactured_position(K, xq, Pa, xg, xm);
+      manufactured_xdot(K, xm, Pa, xd);
       for (int d = 0; d < 3; ++d) disp[d] = K.dt * xd[d];
     }
     for (int d = 0; d < 3; ++d) out[d * NP + p] = (float)(disp[d] * K.inv_h[d]);
@@ -710,55 +711,58 @@ __global__ void __launch_bounds__(kBlock) k_export_mixed(SimConst K, const int* 
 
 // Error norms of the mixed state: positions rebuilt in FP64, manufactured
 // values from FP64 roots, FP64 reductions (same fixed grid and order as
-// k_err_particles_f64).
-__global__ void __launch_bounds__(kBlock) k_err_particles_mixed(SimConst K, double t, const int* key,
-                                                                const float* off, const float* vf,
-                                                                const int* id, double* part,
-                                                                int* flags) {
+// k_err_particles_f64).  Bound by the FP64 instructions of the roots; positions
+// and velocities apart, for the roots' polynomial constants stay in registers
+// over the loop and in one kernel those of both filled the 256 of a thread (one
+// wave per SIMD).  2^23 particles: 1307 us -> 200 + 415 (configuration
+// family), 8780 -> 295 + 810 (paper's).
+__global__ void __launch_bounds__(kBlock) k_err_positions_mixed(SimConst K, double t, const int* key,
+                                                                const float* off, const int* id,
+                                                                double* part, int* flags) {
   key = mem(K, key);
   off = mem(K, off);
+  id = mem(K, id);
+  part = mem(K, part);
+  flags = mem(K, flags);
+  __shared__ double sh[kWaves];
+  double s2[3] = {0, 0, 0}, mx[3] = {0, 0, 0};
+  bool bad = false;
+  const PaperTime P = paper_time(K, t);
+  for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < K.np;
+       i += (int64_t)gridDim.x * kBlock) {
+    double xq[3], xm[3], xp[3];
+    position_uniforms(K, id[i], xq);
+    int cc[3];
+    node_coords(K, key[i], cc[0], cc[1], cc[2]);
+    for (int d = 0; d < 3; ++d) xp[d] = ((double)cc[d] + (double)off[d * K.np + i]) * K.h[d];
+    manufactured_position(K, xq, P, xp, xm);
+    for (int d = 0; d < 3; ++d) err_add(wrapped_error(xp[d] - xm[d], K.L[d]), s2[d], mx[d], bad);
+  }
+  if (bad) atomicOr(&flags[kFlagNonFinite], 1);
+  err_row<3>(s2, mx, part, 0, sh);
+}
+
+template <bool CFG>  // the configuration family's normal velocities, else Sec. 5.2's
+__global__ void __launch_bounds__(kBlock) k_err_velocities_mixed(SimConst K, double t, const float* vf,
+                                                                 const int* id, double* part,
+                                                                 int* flags) {
   vf = mem(K, vf);
   id = mem(K, id);
   part = mem(K, part);
   flags = mem(K, flags);
   __shared__ double sh[kWaves];
-  double s2[6] = {0, 0, 0, 0, 0, 0}, mx[6] = {0, 0, 0, 0, 0, 0};
+  double s2[3] = {0, 0, 0}, mx[3] = {0, 0, 0};
   bool bad = false;
   for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < K.np;
        i += (int64_t)gridDim.x * kBlock) {
-    double xq[3], xv[3], xm[3], a[3], vm[3], vd[3], e[6];
-    position_uniforms(K, id[i], xq);
+    double xv[3], a[3], vm[3], vd[3];
     velocity_uniforms(K, id[i], xv);
-    int c = key[i];
-    int cc[3];
-    node_coords(K, c, cc[0], cc[1], cc[2]);
-    double xp[3];
-    for (int d = 0; d < 3; ++d) xp[d] = ((double)cc[d] + (double)off[d * K.np + i]) * K.h[d];
-    manufactured_position(K, xq, t, xp, xm);
-    velocity_shape(K, xv, a);
+    for (int d = 0; d < 3; ++d) a[d] = CFG ? normal_quantile(xv[d]) : paper_a(xv[d]);
     manufactured_velocity(K, a, t, vm, vd);
-    for (int d = 0; d < 3; ++d) {
-      double ex = xp[d] - xm[d];
-      if (ex >= 0.5 * K.L[d]) ex -= K.L[d];
-      if (ex < -0.5 * K.L[d]) ex += K.L[d];
-      e[d] = ex;
-      e[3 + d] = (double)vf[d * K.np + i] - vm[d];
-    }
-    for (int a2 = 0; a2 < 6; ++a2) {
-      bad |= !isfinite(e[a2]);
-      s2[a2] += e[a2] * e[a2];
-      mx[a2] = fmax(mx[a2], fabs(e[a2]));
-    }
+    for (int d = 0; d < 3; ++d) err_add((double)vf[d * K.np + i] - vm[d], s2[d], mx[d], bad);
   }
   if (bad) atomicOr(&flags[kFlagNonFinite], 1);
-  for (int a2 = 0; a2 < 6; ++a2) {
-    double s = block_sum(s2[a2], sh);
-    double m = block_max(mx[a2], sh);
-    if (threadIdx.x == 0) {
-      part[blockIdx.x * 14 + a2] = s;
-      part[blockIdx.x * 14 + 7 + a2] = m;
-    }
-  }
+  err_row<3>(s2, mx, part, 3, sh);
 }
 
 }  // namespace pic

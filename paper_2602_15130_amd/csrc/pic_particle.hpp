@@ -1099,20 +1099,22 @@ __global__ void __launch_bounds__(kBlock) k_paper_drift_f64(SimConst K, PartArgs
   }
   const int64_t NP = K.np;
   const double dt = K.dt;
-  const double t0 = (double)a.na * dt, th = ((double)a.na + 0.5) * dt, t1 = ((double)a.na + 1.0) * dt;
+  // (isolation mode: at both ends of the step, else at its middle)
+  const PaperTime Pa = paper_time(K, ((double)a.na + (K.isolate ? 0.0 : 0.5)) * dt);
+  const PaperTime Pb = paper_time(K, ((double)a.na + 1.0) * dt);
   for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < NP;
        p += (int64_t)gridDim.x * blockDim.x) {
     double xq[3], h[3];
     position_uniforms(K, a.id[p], xq);
     if (K.isolate) {
       double xa[3], xb[3];
-      manufactured_position(K, xq, t0, nullptr, xa);
-      manufactured_position(K, xq, t1, nullptr, xb);
+      manufactured_position(K, xq, Pa, nullptr, xa);
+      manufactured_position(K, xq, Pb, nullptr, xb);
       for (int d = 0; d < 3; ++d) h[d] = xb[d] - xa[d];
     } else {
       double xm[3], xd[3];
-      manufactured_position(K, xq, th, nullptr, xm);
-      manufactured_xdot(K, xm, th, xd);
+      manufactured_position(K, xq, Pa, nullptr, xm);
+      manufactured_xdot(K, xm, Pa, xd);
       for (int d = 0; d < 3; ++d) h[d] = dt * xd[d];
     }
     for (int d = 0; d < 3; ++d) out[d * NP + p] = h[d];
