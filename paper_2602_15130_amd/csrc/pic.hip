@@ -434,13 +434,22 @@ int scan_counts(pic_ctx* c) {
   return PIC_OK;
 }
 
-// Sort the current buffer (keys, slots and counts already computed) into the other.
-int sort_particles(pic_ctx* c) {
-  StageTimer tm(c, PIC_STAGE_SORT);
+// The particles bucketed by cell (keys, slots and counts already computed): the
+// source index and the cell of every slot.
+int bucket_particles(pic_ctx* c) {
   TRY(scan_counts(c));
   int np = (int)c->K.np;
   k_scatter<<<G(c, (unsigned)(((int64_t)np + kBlock * kScatterPer - 1) / (kBlock * kScatterPer))),
               kBlock, 0, c->stream>>>(c->key, c->slot, c->cstart, c->tidx, c->tkey, np, c->mstride);
+  LAUNCH_CHECK(c, "scatter");
+  return PIC_OK;
+}
+
+// The current buffer into the other, each cell's particles in the order of
+// their source indices; bucketed: the current buffer already holds them slot
+// by slot (the initial state), tidx their ids.
+int order_particles(pic_ctx* c, bool bucketed) {
+  int np = (int)c->K.np;
   int s = c->cur, d = 1 - c->cur;
   const int ntiles = (int)((c->K.np + kTileB - 1) / kTileB);
   // the fused step deposits each tile as it is moved (cell moments for the
@@ -451,18 +460,25 @@ int sort_particles(pic_ctx* c) {
     kfn<<<G(c, ntiles), kTileThreads, 0, c->stream>>>(c->K, c->tile_c0, c->tile_s0, c->tidx, c->tkey,
                                                  c->cstart, c->x[s], c->v[s], c->sh[s], c->id[s],
                                                  c->x[d], c->v[d], c->sh[d], c->id[d], c->key,
-                                                 (double*)c->mom, np, c->flags);
+                                                 (double*)c->mom, np, bucketed, c->flags);
   } else {
     auto kfn = dep ? k_order_tiles<float, true> : k_order_tiles<float, false>;
     kfn<<<G(c, ntiles), kTileThreads, 0, c->stream>>>(c->K, c->tile_c0, c->tile_s0, c->tidx, c->tkey,
                                                  c->cstart, c->off[s], c->vf[s], c->asf[s],
                                                  c->id[s], c->off[d], c->vf[d], c->asf[d],
-                                                 c->id[d], c->key, (float*)c->mom, np, c->flags);
+                                                 c->id[d], c->key, (float*)c->mom, np, bucketed, c->flags);
   }
   c->mom_ready = dep;
   LAUNCH_CHECK(c, "sort");
   c->cur = d;
   return PIC_OK;
+}
+
+// Sort the current buffer (keys, slots and counts already computed) into the other.
+int sort_particles(pic_ctx* c) {
+  StageTimer tm(c, PIC_STAGE_SORT);
+  TRY(bucket_particles(c));
+  return order_particles(c, false);
 }
 
 template <int MODE>
@@ -1427,16 +1443,19 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
           K, c->low, (double*)c->low.tab, (double*)c->low.mu);
       LAUNCH_CHECK(c, "low-mode tables");
     }
-    // unsorted initial state in buffer 1, sorted into buffer 0
+    // initial state bucketed by cell in buffer 1, ordered into buffer 0
     c->cur = 1;
+    const unsigned g = grid_for(K.np);
+    k_init_cells<<<G(c, g), kBlock, 0, c->stream>>>(K, c->key, c->slot, c->count);
+    LAUNCH_CHECK(c, "initial cells");
+    TRY(bucket_particles(c));
     if (c->precision == PIC_FP64)
-      k_init_f64<<<G(c, grid_for(K.np)), kBlock, 0, c->stream>>>(K, c->x[1], c->v[1], c->sh[1], c->id[1],
-                                                           c->key, c->slot, c->count);
+      k_init_f64<<<G(c, g), kBlock, 0, c->stream>>>(K, c->tidx, c->x[1], c->v[1], c->sh[1], c->id[1]);
     else
-      k_init_mixed<<<G(c, grid_for(K.np)), kBlock, 0, c->stream>>>(K, c->off[1], c->vf[1], c->asf[1],
-                                                             c->id[1], c->key, c->slot, c->count);
+      k_init_mixed<<<G(c, g), kBlock, 0, c->stream>>>(K, c->tidx, c->off[1], c->vf[1], c->asf[1],
+                                                      c->id[1]);
     LAUNCH_CHECK(c, "init");
-    TRY(sort_particles(c));
+    TRY(order_particles(c, true));
     TRY(field_solve(c, 0.0));
     return PIC_OK;
   };

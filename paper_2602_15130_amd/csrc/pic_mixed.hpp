@@ -34,39 +34,29 @@ struct MixConst {
 // Initial state (eq. mms_sol): FP64 roots, then cell + FP32 offset.  An offset
 // that would round up to 1 is kept just below it, so the cell is the one the
 // FP64 position falls in.
-__global__ void __launch_bounds__(kBlock) k_init_mixed(SimConst K, float* off, float* vf, float* ash,
-                                                       int* id, int* key, int* slot, int* count) {
+__global__ void __launch_bounds__(kBlock) k_init_mixed(SimConst K, const int* ids, float* off,
+                                                       float* vf, float* ash, int* id) {
+  ids = mem(K, ids);
   off = mem(K, off);
   vf = mem(K, vf);
   ash = mem(K, ash);
   id = mem(K, id);
-  key = mem(K, key);
-  slot = mem(K, slot);
-  count = mem(K, count);
-  int64_t p = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  bool valid = p < K.np;
-  int kk = 0;
-  if (valid) {
-    double xi[6], xm[3], a[3];
-    init_uniforms(K, p, xi);
-    manufactured_position(K, xi, 0.0, nullptr, xm);
-    velocity_shape(K, xi + 3, a);
-    double vm[3], vd[3];
-    manufactured_velocity(K, a, 0.0, vm, vd);
-    int c[3];
-    double o[3];
-    locate(K, xm, c, o);
-    kk = lin(K, c[0], c[1], c[2]);
-    for (int d = 0; d < 3; ++d) {
-      off[d * K.np + p] = fminf((float)o[d], kOneBelow);
-      vf[d * K.np + p] = (float)vm[d];
-      ash[d * K.np + p] = (float)a[d];
-    }
-    id[p] = (int)p;
-    key[p] = kk;
+  int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+  if (j >= K.np) return;
+  const int p = ids[j];
+  double xi[6], xm[3], a[3], vm[3], vd[3], o[3];
+  int c[3];
+  init_uniforms(K, p, xi);
+  manufactured_position(K, xi, 0.0, nullptr, xm);
+  velocity_shape(K, xi + 3, a);
+  manufactured_velocity(K, a, 0.0, vm, vd);
+  locate(K, xm, c, o);
+  for (int d = 0; d < 3; ++d) {
+    off[d * K.np + j] = fminf((float)o[d], kOneBelow);
+    vf[d * K.np + j] = (float)vm[d];
+    ash[d * K.np + j] = (float)a[d];
   }
-  int s = wave_aggregated_slot(count, kk, valid);
-  if (valid) slot[p] = s;
+  id[j] = p;
 }
 
 // Positions given by the caller (FP64) as cell + FP32 offset, wrapped as in

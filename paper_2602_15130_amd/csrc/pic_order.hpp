@@ -29,7 +29,7 @@ __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const 
                                                               const T* xs, const T* vs,
                                                               const T* as, const int* ids, T* xd,
                                                               T* vd, T* ad, int* idd, int* keyd,
-                                                              T* mom, int n, int* flags) {
+                                                              T* mom, int n, int bucketed, int* flags) {
   tile_c0 = mem(K, tile_c0);
   tile_s0 = mem(K, tile_s0);
   tidx = mem(K, tidx);
@@ -55,14 +55,14 @@ __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const 
   if (!lds) {
     for (int j = threadIdx.x; j < ns; j += kTileThreads) {
       const int slot = s0 + j, my = tidx[slot];
-      const int dst = order_dst(tidx, tkey, cstart, slot, flags);
+      const int dst = order_dst(tidx, tkey, cstart, slot, flags), src = bucketed ? slot : my;
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        xd[(int64_t)d * n + dst] = xs[(int64_t)d * n + my];
-        vd[(int64_t)d * n + dst] = vs[(int64_t)d * n + my];
-        ad[(int64_t)d * n + dst] = as[(int64_t)d * n + my];
+        xd[(int64_t)d * n + dst] = xs[(int64_t)d * n + src];
+        vd[(int64_t)d * n + dst] = vs[(int64_t)d * n + src];
+        ad[(int64_t)d * n + dst] = as[(int64_t)d * n + src];
       }
-      idd[dst] = ids[my];
+      idd[dst] = ids[src];
       keyd[dst] = tkey[slot];
     }
     if (!DEP) return;
@@ -86,13 +86,14 @@ __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const 
         lidx[j] = my[q];
         cs[q] = cstart[cc[q]] - s0;
         ce[q] = cstart[cc[q] + 1] - s0;
+        const int src = bucketed ? s0 + j : my[q];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-          sv[q][d] = xs[(int64_t)d * n + my[q]];
-          sv[q][3 + d] = vs[(int64_t)d * n + my[q]];
-          sv[q][6 + d] = as[(int64_t)d * n + my[q]];
+          sv[q][d] = xs[(int64_t)d * n + src];
+          sv[q][3 + d] = vs[(int64_t)d * n + src];
+          sv[q][6 + d] = as[(int64_t)d * n + src];
         }
-        idv[q] = ids[my[q]];
+        idv[q] = ids[src];
       }
     }
     __syncthreads();

@@ -51,3 +51,31 @@ def test_initial_state_solves_its_cdfs(family):
         else:
             G = 0.5 * special.erfc(-m) - m * np.exp(-m * m) / np.sqrt(np.pi)
             np.testing.assert_allclose(G, p, rtol=0, atol=16 * EPS)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("nc,np_", [((3, 3, 3), 1), ((3, 4, 5), 300), ((3, 3, 3), 19001),
+                                    ((3, 3, 3), 70001), ((16, 16, 16), 4097)])
+def test_initial_state_is_bucketed_and_ordered(nc, np_, precision):
+    """Cells of every size (empty, one tile, larger than a tile's LDS slots): the
+    particles of a cell in the order of their ids, each in its own cell, and
+    velocities that depend on the id alone (bit for bit those of another mesh)."""
+    from paper_2602_15130_amd import pic as P
+
+    def state(nc):
+        disc = {"nc": nc, "np": np_, "dt": 1e-3, "navg": 1, "cg_tol": 1e-12, "cg_max_iter": 1000}
+        with P.Sim(W.cfg_problem(collisions=False), disc, 7, 2, precision) as g:
+            return (np.asarray(g.get(P.STATE_ID)), np.asarray(g.get(P.STATE_X)).reshape(3, np_),
+                    np.asarray(g.get(P.STATE_V)).reshape(3, np_), np.asarray(g.get(P.STATE_CELL_START)))
+
+    i, x, v, start = state(nc)
+    i2, x2, v2, _ = state((4, 3, 5))
+    assert np.array_equal(np.sort(i), np.arange(np_)) and start[0] == 0 and start[-1] == np_
+    cell = np.repeat(np.arange(len(start) - 1), np.diff(start))
+    c = [np.minimum(np.floor(x[d] * nc[d]), nc[d] - 1).astype(int) for d in range(3)]
+    assert np.array_equal((c[2] * nc[1] + c[1]) * nc[0] + c[0], cell)
+    same = cell[1:] == cell[:-1]
+    assert np.all(i[1:][same] > i[:-1][same])
+    np.testing.assert_array_equal(v[:, np.argsort(i)], v2[:, np.argsort(i2)])
+    if precision == "fp64":
+        np.testing.assert_array_equal(x[:, np.argsort(i)], x2[:, np.argsort(i2)])
