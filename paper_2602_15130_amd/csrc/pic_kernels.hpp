@@ -1336,6 +1336,30 @@ __global__ void __launch_bounds__(kBlock) k_err_particles_f64(SimConst K, double
   err_row<6>(s2, mx, part, 0, sh);
 }
 
+// What a query of the state checks, over all members of an ensemble.
+struct MembersAny {
+  int flags[kFlagCount];
+  unsigned long long gmax;
+};
+__global__ void __launch_bounds__(kBlock) k_members_any(const int* flags, const unsigned long long* cnt,
+                                                        int members, int64_t mstride, MembersAny* out) {
+  __shared__ int f[kFlagCount];
+  __shared__ unsigned long long g;
+  if (threadIdx.x < kFlagCount) f[threadIdx.x] = 0;
+  if (threadIdx.x == 0) g = 0;
+  __syncthreads();
+  for (int m = threadIdx.x; m < members; m += kBlock) {
+    const int* fm = (const int*)((const char*)flags + m * mstride);
+    for (int i = 0; i < kFlagCount; ++i)
+      if (fm[i]) atomicOr(&f[i], fm[i]);
+    const unsigned long long n = *(const unsigned long long*)((const char*)(cnt + kCntGmax) + m * mstride);
+    if (n) atomicAdd(&g, n);
+  }
+  __syncthreads();
+  if (threadIdx.x < kFlagCount) out->flags[threadIdx.x] = f[threadIdx.x];
+  if (threadIdx.x == 0) out->gmax = g;
+}
+
 __global__ void __launch_bounds__(kBlock) k_err_nodes(SimConst K, double t, const double* phi,
                                                       double* part) {
   phi = mem(K, phi);
