@@ -239,6 +239,7 @@ struct pic_ctx {
   bool direct = false;          // all of them (pic_direct.hpp); the CG then only finishes
   size_t direct_lds = 0;        // LDS of the one-launch direct solve, 0 = one launch per transform
   size_t low_lds[3] = {0, 0, 0};  // dynamic LDS of the three pre-solve passes
+  bool defer_empty = false;       // the list of deferred tiles known to be empty (so by the scan)
   bool count_zero = false;        // cell counts known to be zero (left so by the scan)
   bool mom_ready = false;         // cell moments of the current positions deposited by the sort
   bool heavy = false;           // collision calls by k_collide_heavy (many pairs per outcome)
@@ -418,21 +419,27 @@ int zero_counts(pic_ctx* c) {
 }
 
 // Exclusive scan of the cell counts into cell_start; the counts are left at
-// zero and the tile tables of the sorted order are written on the way.
+// zero, the tile tables of the sorted order are written and the list of deferred
+// tiles is emptied on the way.
 int scan_counts(pic_ctx* c) {
   int n = c->K.nn;
   int nb = (n + kScanTile - 1) / kScanTile;
   TileInit ti;
+  ti.defer = c->defer;
   ti.c0 = c->tile_c0;
   ti.s0 = c->tile_s0;
   ti.ntiles = (int)((c->K.np + kTileB - 1) / kTileB);
   ti.ncell = n;
   ti.np = (int)c->K.np;
   k_scan_local<<<G(c, nb), kBlock, 0, c->stream>>>(c->count, c->cstart, c->bsum, n, ti, c->mstride);
-  k_scan_blocks<<<G(c, 1), kBlock, 0, c->stream>>>(c->bsum, nb, c->cstart, n, c->mstride);
-  k_scan_add<<<G(c, nb), kBlock, 0, c->stream>>>(c->cstart, c->bsum, n, c->count, ti, c->mstride);
+  const int scanned = nb > kScanDirect;
+  if (scanned)
+    k_scan_blocks<<<G(c, 1), kBlock, 0, c->stream>>>(c->bsum, nb, c->cstart, n, c->mstride);
+  k_scan_add<<<G(c, nb), kBlock, 0, c->stream>>>(c->cstart, c->bsum, scanned, n, c->count, ti,
+                                                 c->mstride);
   LAUNCH_CHECK(c, "scan");
   c->count_zero = true;
+  c->defer_empty = true;
   return PIC_OK;
 }
 
@@ -821,6 +828,11 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
     else
       k_draw_pairs<double><<<gd, 64 * kDrawWaves, 0, c->stream>>>(K, a, per);
     LAUNCH_CHECK(c, "draw pairs");
+    c->defer_empty = true;
+  }
+  if (!full) {  // an empty list of deferred tiles
+    if (!c->defer_empty) TRY(fill(c, c->defer, 0, 1));
+    c->defer_empty = false;
   }
   if (c->precision == PIC_MIXED) {
     const MixConst M = mix_const(K, a);  // (a captured step computes them on the device)
@@ -836,7 +848,6 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
     }
     const int s = c->cur;
     if (!full) {
-      TRY(fill(c, c->defer, 0, 1));  // an empty deferral list
       fm[first]<<<G(c, tiles), dim3(kTileThreads), 0, c->stream>>>(K, M, a, c->off[s], c->vf[s],
                                                               c->asf[s], c->E32);
       LAUNCH_CHECK(c, "particles (mixed, lean)");
@@ -847,7 +858,6 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
     return PIC_OK;
   }
   if (!full) {
-    TRY(fill(c, c->defer, 0, 1));  // an empty deferral list
     fns.f64[first]<<<G(c, tiles), kTileThreads, 0, c->stream>>>(K, a);
     LAUNCH_CHECK(c, "particles (lean)");
   }
@@ -973,35 +983,31 @@ int one_step(pic_ctx* c) {
 
 // The pair counts into the counters, before the host reads those.
 int fold_counters(pic_ctx* c) {
-  k_fold_counters<<<G(c, 1), kCntSpread, 0, c->stream>>>(c->cnt, c->spread, c->mstride);
+  k_fold_counters<<<G(c, 1), kCntSpread, 0, c->stream>>>(c->cnt, c->spread, c->flags, c->any,
+                                                         c->mstride);
   LAUNCH_CHECK(c, "fold counters");
   return PIC_OK;
 }
 
-// The flags raised, or (gmax) the pairs above g_max, over all members; waits for
-// the stream.  Put together on the device where there are several: a copy to the
-// host is about 9 us, and a query of one member of 16 made 33 of them.
-int members_any(pic_ctx* c, bool gmax, MembersAny& out) {
+// The flags raised and, right after fold_counters (folded) or with several members,
+// the pairs above g_max, over all members; waits for the stream.  A copy to the
+// host is about 9 us, so one has to do: several members' are put together on
+// the device (a query of one member of 16 made 33 copies).
+int members_any(pic_ctx* c, bool folded, MembersAny& out) {
+  out = MembersAny{};
   if (c->members > 1) {
     k_members_any<<<1, kBlock, 0, c->stream>>>(c->flags, c->cnt, c->members, c->mstride, c->any);
     LAUNCH_CHECK(c, "flags");
   }
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  if (c->members > 1) {
+  if (c->members > 1 || folded)
     HIP_TRY(c, hipMemcpy(&out, c->any, sizeof(out), hipMemcpyDeviceToHost));
-    return PIC_OK;
-  }
-  if (gmax)
-    HIP_TRY(c, hipMemcpy(&out.gmax, c->cnt + kCntGmax, sizeof(out.gmax), hipMemcpyDeviceToHost));
   else
     HIP_TRY(c, hipMemcpy(out.flags, c->flags, sizeof(out.flags), hipMemcpyDeviceToHost));
   return PIC_OK;
 }
 
-// Read back flags raised by earlier asynchronous work.
-int check_flags(pic_ctx* c) {
-  MembersAny any{};
-  TRY(members_any(c, false, any));
+int flags_status(pic_ctx* c, const MembersAny& any) {
   const int* f = any.flags;
   if (f[kFlagBarrier]) {
     c->err = "grid barrier timed out in the Poisson solver";
@@ -1022,11 +1028,15 @@ int check_flags(pic_ctx* c) {
   return PIC_OK;
 }
 
+int check_flags(pic_ctx* c) {
+  MembersAny any;
+  TRY(members_any(c, false, any));
+  return flags_status(c, any);
+}
+
 // PIC_WARN_GMAX once a candidate pair with g > g_max has been seen since
-// initialisation (stream idle).
-int gmax_warning(pic_ctx* c) {
-  MembersAny any{};
-  TRY(members_any(c, true, any));
+// initialisation.
+int gmax_warning(pic_ctx* c, const MembersAny& any) {
   const unsigned long long n = any.gmax;
   if (n > 0) {
     c->err = std::to_string(n) + " candidate pairs had a relative speed above g_max";
@@ -1102,7 +1112,9 @@ int errors_into(pic_ctx* c, pic_error_norms* out, double* epart, double* npart, 
   k_err_final<<<G(c, 1), kBlock, 0, c->stream>>>(K, epart, nbp, npart, nbn, norms);
   LAUNCH_CHECK(c, "errors");
   TRY(fold_counters(c));  // (for the warning below)
-  TRY(check_flags(c));
+  MembersAny any;
+  TRY(members_any(c, true, any));
+  TRY(flags_status(c, any));
   for (int m = 0; m < c->members; ++m) {
     double h[14];
     HIP_TRY(c, hipMemcpy(h, (const char*)norms + (int64_t)m * c->mstride, sizeof(h),
@@ -1117,7 +1129,7 @@ int errors_into(pic_ctx* c, pic_error_norms* out, double* epart, double* npart, 
       }
     }
   }
-  return gmax_warning(c);
+  return gmax_warning(c, any);
 }
 
 }  // namespace
@@ -1442,7 +1454,6 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
   auto init = [&]() -> int {
     const SimConst& K = c->K;
     TRY(fill<int>(c, c->flags, 0, kFlagCount));
-    TRY(fill<int>(c, c->defer, 0, 1));
     TRY(fill<unsigned long long>(c, c->cnt, 0ull, kCntCount));
     TRY(fill<unsigned long long>(c, c->spread, 0ull, kCntSpread * kCntStride));
     c->count_zero = false;
@@ -1538,7 +1549,7 @@ int pic_collide(pic_ctx* c, int call, double t, double* dv_avg, double* dv_src, 
     return PIC_EINVAL;
   }
   const SimConst& K = c->K;
-  TRY(fill<unsigned long long>(c, c->cnt + kCntPairLog, 0ull, 1));
+  if (pairlog_cap > 0) TRY(fill<unsigned long long>(c, c->cnt + kCntPairLog, 0ull, 1));
   if (c->fused) {
     PartArgs a = part_args(c);
     a.mode = kCollideOnly;
@@ -1558,14 +1569,16 @@ int pic_collide(pic_ctx* c, int call, double t, double* dv_avg, double* dv_src, 
     LAUNCH_CHECK(c, "source");
   }
   TRY(fold_counters(c));  // (for the warning below)
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  MembersAny any;
+  TRY(members_any(c, true, any));
   if (pairlog_n) {
     unsigned long long nlog = 0;
-    HIP_TRY(c, hipMemcpy(&nlog, c->cnt + kCntPairLog, sizeof(nlog), hipMemcpyDeviceToHost));
+    if (pairlog_cap > 0)
+      HIP_TRY(c, hipMemcpy(&nlog, c->cnt + kCntPairLog, sizeof(nlog), hipMemcpyDeviceToHost));
     *pairlog_n = (int64_t)nlog;
   }
-  TRY(check_flags(c));
-  return gmax_warning(c);
+  TRY(flags_status(c, any));
+  return gmax_warning(c, any);
 }
 
 int pic_errors(pic_ctx* c, pic_error_norms* out) {

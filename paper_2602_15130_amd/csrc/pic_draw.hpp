@@ -40,6 +40,7 @@ __global__ void __launch_bounds__(64 * kDrawWaves) k_draw_pairs(SimConst K, Part
     a.nb = *K.stepc;
     a.na = a.nb + 1;
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.defer[0] = 0;  // for the pass that follows
   __shared__ DrawLds lds[kDrawWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   DrawLds& Q = lds[wave];

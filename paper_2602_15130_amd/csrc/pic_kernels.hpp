@@ -157,17 +157,31 @@ __global__ void k_fill(T* p, T v, int64_t n, int64_t mstride) {
     p[i] = v;
 }
 
-// Moves the spread counts into the counters (one workgroup per member).
+// What a query of the state checks.
+struct MembersAny {
+  int flags[kFlagCount];
+  unsigned long long gmax;
+};
+
+// Moves the spread counts into the counters and leaves what a query checks in
+// one place (one workgroup per member).
 __global__ void __launch_bounds__(kCntSpread) k_fold_counters(unsigned long long* cnt,
                                                               unsigned long long* spread,
+                                                              const int* flags, MembersAny* any,
                                                               int64_t mstride) {
   cnt = mem_z(mstride, cnt);
   spread = mem_z(mstride, spread);
+  flags = mem_z(mstride, flags);
+  any = mem_z(mstride, any);
   unsigned long long* c = spread + threadIdx.x * kCntStride;
   for (int i = 0; i < 2; ++i) {
     if (c[i]) atomicAdd(&cnt[i], c[i]);
     c[i] = 0ull;
   }
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x < kFlagCount) any->flags[threadIdx.x] = flags[threadIdx.x];
+  if (threadIdx.x == 0) any->gmax = atomicAdd(&cnt[kCntGmax], 0ull);
 }
 
 // ---------------------------------------------------------------------------
@@ -235,12 +249,18 @@ __global__ void __launch_bounds__(kBlock) k_count(const int* key, int* slot, int
   if (valid) slot[i] = s;
 }
 
-// Exclusive scan of n ints in three passes; 1024 items per block.
+// Exclusive scan of n ints, 1024 items per block: the blocks by themselves, then
+// the sum of the blocks before each.  Up to kScanDirect blocks every workgroup
+// of the second pass adds those up itself (a launch of its own for them took 4.7
+// us, these loads under 1 us); their number grows with the square, so beyond
+// that one workgroup scans the block sums in between.
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kBlock * kScanItems;
+constexpr int kScanDirect = 2048;
 
-// Tile tables of the sort, filled before the third pass writes their bounds.
+// Tile tables of the sort, filled before the last pass writes their bounds.
 struct TileInit {
+  int* defer;  // the fused pass's list of deferred tiles, emptied on the way
   int* c0;     // first cell per tile, filled with the cell count
   int* s0;     // first particle per tile, filled with the particle count
   int ntiles;  // entries 0..ntiles
@@ -255,6 +275,8 @@ __global__ void __launch_bounds__(kBlock) k_scan_local(const int* in, int* out, 
   bsum = mem_z(mstride, bsum);
   ti.c0 = mem_z(mstride, ti.c0);
   ti.s0 = mem_z(mstride, ti.s0);
+  ti.defer = mem_z(mstride, ti.defer);
+  if (blockIdx.x == 0 && threadIdx.x == 0) ti.defer[0] = 0;
   for (int t = blockIdx.x * kBlock + threadIdx.x; t <= ti.ntiles; t += gridDim.x * kBlock) {
     ti.c0[t] = ti.ncell;
     ti.s0[t] = ti.np;
@@ -313,21 +335,35 @@ __global__ void __launch_bounds__(kBlock) k_scan_blocks(int* bsum, int nb, int* 
   if (threadIdx.x == 0) out[n] = carry;
 }
 
-// Pass 3: adds the block prefixes, giving the cell starts; resets the counts
+// Last pass: adds the block prefixes (bsum: the blocks' sums, or, scanned, those
+// prefixes themselves with the total in place), giving the cell starts; resets the counts
 // to zero for the next counting pass; and writes the bounds of the cell-aligned
 // tiles, tile_c0[t] = min{c : cstart[c] >= t kTileB} and tile_s0[t] =
 // cstart[tile_c0[t]]: with lo = cstart[j] and hi = cstart[j + 1] = lo + count[j],
 // cell c = j + 1 is that minimum for every t with lo < t kTileB <= hi.  Tile 0
 // starts at cell 0; tiles past the end keep the fill of pass 1.
-__global__ void __launch_bounds__(kBlock) k_scan_add(int* out, const int* bsum, int n, int* count,
-                                                     TileInit ti, int64_t mstride) {
+__global__ void __launch_bounds__(kBlock) k_scan_add(int* out, const int* bsum, int scanned, int n,
+                                                     int* count, TileInit ti, int64_t mstride) {
   out = mem_z(mstride, out);
   bsum = mem_z(mstride, bsum);
   count = mem_z(mstride, count);
   ti.c0 = mem_z(mstride, ti.c0);
   ti.s0 = mem_z(mstride, ti.s0);
   int base = blockIdx.x * kScanTile;
-  int add = bsum[blockIdx.x];
+  int add;
+  if (scanned) {
+    add = bsum[blockIdx.x];
+  } else {
+    __shared__ int sh[kWaves];
+    int s = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kBlock) s += bsum[i];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    add = 0;
+    for (int w = 0; w < kWaves; ++w) add += sh[w];
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = add + bsum[blockIdx.x];
+  }
   for (int j = threadIdx.x; j < kScanTile; j += kBlock) {
     const int jj = base + j;
     if (jj >= n) continue;
@@ -1337,10 +1373,6 @@ __global__ void __launch_bounds__(kBlock) k_err_particles_f64(SimConst K, double
 }
 
 // What a query of the state checks, over all members of an ensemble.
-struct MembersAny {
-  int flags[kFlagCount];
-  unsigned long long gmax;
-};
 __global__ void __launch_bounds__(kBlock) k_members_any(const int* flags, const unsigned long long* cnt,
                                                         int members, int64_t mstride, MembersAny* out) {
   __shared__ int f[kFlagCount];
