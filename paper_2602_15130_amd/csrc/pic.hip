@@ -535,8 +535,8 @@ int field_solve(pic_ctx* c, double t) {
         k_deposit_tiles_f64<<<G(c, ntiles), kTileThreads, 0, c->stream>>>(K, c->x[c->cur], c->cstart,
                                                               c->tile_c0, (double*)c->mom);
       else if (!have_mom)
-        k_deposit_moments_f64<<<nbn, kBlock, 0, c->stream>>>(K, c->x[c->cur], c->cstart,
-                                                             (double*)c->mom);
+        k_deposit_moments_f64<<<(K.nn + kWaves - 1) / kWaves, kBlock, 0, c->stream>>>(
+            K, c->x[c->cur], c->cstart, (double*)c->mom);
       k_node_rhs<double><<<G(c, nbn), kBlock, 0, c->stream>>>(K, (const double*)c->mom, t, c->rho, c->b,
                                                         c->partA, c->phi, c->direct ? c->dir.w : nullptr,
                                                         c->capturing ? c->stepc : nullptr);

