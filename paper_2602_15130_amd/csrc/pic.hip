@@ -237,7 +237,8 @@ struct pic_ctx {
   size_t cg_lds = 0;            // padded brick, bytes of LDS
   int low_k = 0;                // Fourier modes per axis solved exactly before the CG
   bool direct = false;          // all of them (pic_direct.hpp); the CG then only finishes
-  size_t direct_lds = 0;        // LDS of the one-launch direct solve, 0 = one launch per transform
+  size_t direct_lds = 0;        // LDS of the one-launch direct solve, 0 = several launches
+  size_t direct_plane = 0, direct_columns = 0;  // LDS of the three-launch one, 0 = a launch per transform
   size_t low_lds[3] = {0, 0, 0};  // dynamic LDS of the three pre-solve passes
   bool defer_empty = false;       // the list of deferred tiles known to be empty (so by the scan)
   bool count_zero = false;        // cell counts known to be zero (left so by the scan)
@@ -509,6 +510,13 @@ void direct_axis(pic_ctx* c) {
 int direct_solve(pic_ctx* c) {
   if (c->direct_lds > 0) {
     k_direct_small<<<G(c, 1), kDirectSmallThreads, c->direct_lds, c->stream>>>(c->K, c->dir);
+  } else if (c->direct_plane > 0) {
+    const SimConst& K = c->K;
+    const dim3 planes = G(c, K.nc[2]);
+    const unsigned columns = (K.nc[0] * K.nc[1] + kDirectColumns - 1) / kDirectColumns;
+    k_direct_plane<0><<<planes, kDirectPlaneThreads, c->direct_plane, c->stream>>>(K, c->dir);
+    k_direct_columns<<<G(c, columns), kDirectColumnThreads, c->direct_columns, c->stream>>>(K, c->dir);
+    k_direct_plane<1><<<planes, kDirectPlaneThreads, c->direct_plane, c->stream>>>(K, c->dir);
   } else {
     direct_axis<0>(c);
     direct_axis<1>(c);
@@ -1448,6 +1456,16 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
         hipFuncSetAttribute((const void*)k_direct_small, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)need) == hipSuccess)
       c->direct_lds = need;
+    const size_t np = direct_plane_lds(c->K.nc), ncol = direct_column_lds(c->K.nc);
+    auto allow = [](const void* fn, size_t bytes) {
+      return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+    };
+    if (c->direct && np + 512 <= (size_t)lds_cap && ncol + 512 <= (size_t)lds_cap &&
+        allow((const void*)k_direct_plane<0>, np) && allow((const void*)k_direct_plane<1>, np) &&
+        allow((const void*)k_direct_columns, ncol)) {
+      c->direct_plane = np;
+      c->direct_columns = ncol;
+    }
     (void)hipGetLastError();
   }
 

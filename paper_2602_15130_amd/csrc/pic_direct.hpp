@@ -121,7 +121,7 @@ __device__ inline f64x4 mfma_f64(double a, double b, f64x4 c) {
 #endif
 }
 
-// The six transforms, C = A B with A row-major in k and B row-major in n:
+// The six transforms one by one, C = A B with A row-major in k and B row-major in n:
 //   0  x forward   rows (k, j), A = w (the residual), B = transposed table -> u
 //   1  y forward   per z plane, A = table, B = u's plane             -> w
 //   2  z forward   A = table, B = w as [nz][nx ny], scaled           -> u
@@ -221,6 +221,157 @@ __global__ void __launch_bounds__(256) k_direct_axis(SimConst K, DirectArgs D) {
   }
 }
 
+// C = A B over all 16 x 16 tiles of M x N by the NW waves of a workgroup, operands
+// from LDS: A(m, k), B(k, n), and store(m, n, value); k up to a multiple of four,
+// where one of the operands (a table) is zero beyond KK.
+template <int NW, class FA, class FB, class FS>
+__device__ inline void direct_product(int M, int N, int KK, FA A, FB B, FS store) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+  const int tm = (M + 15) / 16, tn = (N + 15) / 16;
+  for (int t = wave; t < tm * tn; t += NW) {
+    const int m0 = (t / tn) * 16, n0 = (t % tn) * 16;
+    const int ma = min(m0 + r, M - 1), nb = min(n0 + r, N - 1);
+    f64x4 c = {0.0, 0.0, 0.0, 0.0};
+    int k = 0;
+    for (; k + 16 <= KK; k += 16) {
+      double a[4], b[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        a[q] = A(ma, k + 4 * q + g);
+        b[q] = B(k + 4 * q + g, nb);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) c = mfma_f64(a[q], b[q], c);
+    }
+    for (; k < KK; k += 4) c = mfma_f64(A(ma, k + g), B(k + g, nb), c);
+    if (n0 + r < N)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (m0 + 4 * v + g < M) store(m0 + 4 * v + g, n0 + r, c[v]);
+  }
+  __syncthreads();
+}
+
+// A table in LDS, rows of stride direct_pitch(n), zero beyond n.
+__host__ __device__ inline int direct_pitch(int n) { return ((n + 3) / 4 * 4) | 1; }
+__host__ __device__ inline int direct_table_lds(int n) { return (n + 3) / 4 * 4 * direct_pitch(n); }
+template <int NT>
+__device__ inline void direct_stage_table(const double* f, int n, double* p) {
+  const int n4 = (n + 3) / 4 * 4, lp = direct_pitch(n);
+  for (int t0 = threadIdx.x; t0 < n4 * n4; t0 += 4 * NT) {  // (four loads in flight)
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = t0 + q * NT, a = t / n4, i = t - a * n4;
+      v[q] = a < n && i < n ? f[a * n + i] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = t0 + q * NT, a = t / n4, i = t - a * n4;
+      if (a < n4) p[a * lp + i] = v[q];
+    }
+  }
+}
+
+// Meshes whose planes fit LDS twice, with the tables of x and y, and whose z table
+// does: three launches instead of six, the transforms of x and y in one
+// (DIR 0 forward, w -> u; 1 backward, w -> added to x), a workgroup of 16 waves
+// per plane, and those of z both ways in the other (u -> w), a workgroup of eight
+// waves per 16 columns.  Bound by launches and by the loads of the tables; a launch
+// per axis is 4 to 7 us for 1 us of products.  Six launches against three: 28
+// and 19 us at 32^3, 35 and 36 at 64^3, where the three gaps between launches
+// that are gone decide (a step 0.8 % faster).
+constexpr int kDirectPlaneThreads = 1024;
+inline size_t direct_plane_lds(const int nc[3]) {
+  return (2 * (size_t)nc[1] * (nc[0] | 1) + direct_table_lds(nc[0]) + direct_table_lds(nc[1])) *
+         sizeof(double);
+}
+constexpr int kDirectColumns = 16, kDirectColumnThreads = 512;
+inline size_t direct_column_lds(const int nc[3]) {
+  return (2 * (size_t)nc[2] * (kDirectColumns + 1) + direct_table_lds(nc[2])) * sizeof(double);
+}
+
+template <int DIR>
+__global__ void __launch_bounds__(kDirectPlaneThreads) k_direct_plane(SimConst K, DirectArgs D) {
+  D = member_view(K, D);
+  extern __shared__ double lds[];
+  __shared__ double sh[kDirectPlaneThreads / 64];
+  const int nx = K.nc[0], ny = K.nc[1], ld = nx | 1, lx = direct_pitch(nx), ly = direct_pitch(ny);
+  double* P = lds;
+  double* Q = P + ny * ld;
+  double* tx = Q + ny * ld;
+  double* ty = tx + direct_table_lds(nx);
+  const int64_t at = (int64_t)blockIdx.x * nx * ny;
+  if (DIR == 0 && blockIdx.x == 0) direct_mean<kDirectPlaneThreads>(K, D, sh);
+  direct_stage_table<kDirectPlaneThreads>(D.f[0], nx, tx);
+  direct_stage_table<kDirectPlaneThreads>(D.f[1], ny, ty);
+  for (int t0 = threadIdx.x; t0 < nx * ny; t0 += 4 * kDirectPlaneThreads) {
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = t0 + q * kDirectPlaneThreads;
+      v[q] = t < nx * ny ? D.w[at + t] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = t0 + q * kDirectPlaneThreads, j = t / nx;
+      if (t < nx * ny) P[j * ld + t - j * nx] = v[q];
+    }
+  }
+  __syncthreads();
+  constexpr int NW = kDirectPlaneThreads / 64;
+  if constexpr (DIR == 0) {
+    direct_product<NW>(ny, nx, nx, [&](int m, int k) { return P[m * ld + min(k, nx - 1)]; },
+                       [&](int k, int n) { return tx[n * lx + k]; },
+                       [&](int m, int n, double v) { Q[m * ld + n] = v; });
+    direct_product<NW>(ny, nx, ny, [&](int m, int k) { return ty[m * ly + k]; },
+                       [&](int k, int n) { return Q[min(k, ny - 1) * ld + n]; },
+                       [&](int m, int n, double v) { D.u[at + m * nx + n] = v; });
+  } else {
+    direct_product<NW>(ny, nx, ny, [&](int m, int k) { return ty[k * ly + m]; },
+                       [&](int k, int n) { return P[min(k, ny - 1) * ld + n]; },
+                       [&](int m, int n, double v) { Q[m * ld + n] = v; });
+    direct_product<NW>(ny, nx, nx, [&](int m, int k) { return Q[m * ld + min(k, nx - 1)]; },
+                       [&](int k, int n) { return tx[k * lx + n]; },
+                       [&](int m, int n, double v) { D.x[at + m * nx + n] += v; });
+  }
+}
+
+__global__ void __launch_bounds__(kDirectColumnThreads) k_direct_columns(SimConst K, DirectArgs D) {
+  D = member_view(K, D);
+  extern __shared__ double lds[];
+  const int nx = K.nc[0], nz = K.nc[2], plane = nx * K.nc[1], lz = direct_pitch(nz);
+  constexpr int ld = kDirectColumns + 1;
+  double* P = lds;
+  double* Q = P + nz * ld;
+  double* tz = Q + nz * ld;
+  const int c0 = blockIdx.x * kDirectColumns, nc = min(kDirectColumns, plane - c0);
+  direct_stage_table<kDirectColumnThreads>(D.f[2], nz, tz);
+  for (int t0 = threadIdx.x; t0 < nz * kDirectColumns; t0 += 4 * kDirectColumnThreads) {
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = t0 + q * kDirectColumnThreads, k = t / kDirectColumns, i = t % kDirectColumns;
+      v[q] = k < nz && i < nc ? D.u[(int64_t)k * plane + c0 + i] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = t0 + q * kDirectColumnThreads, k = t / kDirectColumns;
+      if (k < nz) P[k * ld + t % kDirectColumns] = v[q];
+    }
+  }
+  __syncthreads();
+  constexpr int NW = kDirectColumnThreads / 64;
+  direct_product<NW>(nz, nc, nz, [&](int m, int k) { return tz[m * lz + k]; },
+                     [&](int k, int n) { return P[min(k, nz - 1) * ld + n]; },
+                     [&](int m, int n, double v) {
+                       Q[m * ld + n] = v * direct_scale(K, D, (c0 + n) % nx, (c0 + n) / nx, m);
+                     });
+  direct_product<NW>(nz, nc, nz, [&](int m, int k) { return tz[k * lz + m]; },
+                     [&](int k, int n) { return Q[min(k, nz - 1) * ld + n]; },
+                     [&](int m, int n, double v) { D.w[(int64_t)m * plane + c0 + n] = v; });
+}
+
 // A mesh that fits one workgroup's LDS twice: all six transforms in one launch,
 // one workgroup of 16 waves per member, so that a small solve costs one launch's
 // latency instead of six.  Rows along x have an odd stride (bank spread).
@@ -228,10 +379,7 @@ constexpr int kDirectSmallThreads = 1024;
 inline size_t direct_small_lds(const int nc[3]) {
   const size_t ld = nc[0] | 1, buf = (size_t)nc[2] * nc[1] * ld;
   size_t tab = 0;
-  for (int d = 0; d < 3; ++d) {
-    const size_t p = (nc[d] + 3) / 4 * 4;
-    tab += p * (p | 1);
-  }
+  for (int d = 0; d < 3; ++d) tab += direct_table_lds(nc[d]);
   return (2 * buf + tab) * sizeof(double);
 }
 
@@ -243,23 +391,17 @@ __global__ void __launch_bounds__(kDirectSmallThreads) k_direct_small(SimConst K
   const int ld = nx | 1, pl = ny * ld;  // row and plane stride
   double* P = lds;
   double* Q = P + nz * pl;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x;
   direct_mean<kDirectSmallThreads>(K, D, sh);
-  // the tables, zero beyond n to a multiple of four; lp: row stride
   const double* tab[3];
   int lp[3];
   {
     double* p = Q + nz * pl;
     for (int d = 0; d < 3; ++d) {
-      const int n = K.nc[d], n4 = (n + 3) / 4 * 4;
-      lp[d] = n4 | 1;
-      for (int t = tid; t < n4 * n4; t += kDirectSmallThreads) {
-        const int a = t / n4, i = t % n4;
-        p[a * lp[d] + i] = a < n && i < n ? D.f[d][a * n + i] : 0.0;
-      }
+      direct_stage_table<kDirectSmallThreads>(D.f[d], K.nc[d], p);
       tab[d] = p;
-      p += n4 * lp[d];
+      lp[d] = direct_pitch(K.nc[d]);
+      p += direct_table_lds(K.nc[d]);
     }
   }
   for (int t = tid; t < nz * pl; t += kDirectSmallThreads) {
@@ -268,19 +410,8 @@ __global__ void __launch_bounds__(kDirectSmallThreads) k_direct_small(SimConst K
     Q[t] = 0.0;
   }
   __syncthreads();
-  // C = A B over all 16 x 16 tiles; store(m, n, value) within M x N
   auto product = [&](int M, int N, int KK, auto A, auto B, auto store) {
-    const int tm = (M + 15) / 16, tn = (N + 15) / 16;
-    for (int t = wave; t < tm * tn; t += kDirectSmallThreads / 64) {
-      const int m0 = (t / tn) * 16, n0 = (t % tn) * 16;
-      const int ma = min(m0 + r, M - 1), nb = min(n0 + r, N - 1);
-      f64x4 c = {0.0, 0.0, 0.0, 0.0};
-      for (int k = 0; k < KK; k += 4) c = mfma_f64(A(ma, k + g), B(k + g, nb), c);
-      if (n0 + r < N)
-        for (int v = 0; v < 4; ++v)
-          if (m0 + 4 * v + g < M) store(m0 + 4 * v + g, n0 + r, c[v]);
-    }
-    __syncthreads();
+    direct_product<kDirectSmallThreads / 64>(M, N, KK, A, B, store);
   };
   // (beyond an axis the table is zero; the other operand repeats its last row)
   const int rows = ny * nz;
