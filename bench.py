@@ -55,10 +55,10 @@ def stage_bytes(stage, prob, disc, precision, cg_iters):
         return (sx + sv + (sv + 4 if coll else 0) + sv) * np_ + 28 * nn
     if stage == "drift":         # x, v, a in; x, key, slot out
         return (sx + sv + sa + sx + 4 + 4) * np_ + 4 * nn
-    if stage == "sort":          # scatter slots (key, slot -> index, key); the
-        # ordered move reads the indices and gathers/scatters x, v, a, id; key
+    if stage == "sort":          # scatter slots (key, slot -> index); the ordered
+        # move reads the indices and gathers/scatters x, v, a, id; key
         # out; in the fused step it also writes the cell moments (64 B a cell)
-        return (16 + 8 + 2 * (px + sv + sa + 4) + 4) * np_ + 12 * nn + 64 * nn
+        return (12 + 4 + 2 * (px + sv + sa + 4) + 4) * np_ + 12 * nn + 64 * nn
     if stage == "deposit":       # cell moments in; node charge and right-hand
         # side out, the right-hand side's mean removed
         return 64 * nn + 16 * nn + 16 * nn
@@ -449,7 +449,7 @@ def run_workload(pic, W, torch, workload, steps, warmup):
     dom_bytes = METHOD_BYTES[precision] * disc["np"] if dom == "particle" else impl_bytes
     ach = dom_bytes / dom_s / 1e9
     kernel_names = {"particle": "k_particles_" + ("f64" if precision == "fp64" else "mixed"),
-                    "cg": "k_cg_brick / k_cg (+ low-mode pre-solve)", "sort": "k_order_tiles",
+                    "cg": "k_direct_* (k_cg_brick / k_cg below its rounding)", "sort": "k_order_tiles",
                     "deposit": "k_deposit_tiles"}
     roof = {"bound": "hbm", "kernel": kernel_names.get(dom, dom), "achieved": round(ach, 1),
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),

@@ -450,7 +450,7 @@ int bucket_particles(pic_ctx* c) {
   TRY(scan_counts(c));
   int np = (int)c->K.np;
   k_scatter<<<G(c, (unsigned)(((int64_t)np + kBlock * kScatterPer - 1) / (kBlock * kScatterPer))),
-              kBlock, 0, c->stream>>>(c->key, c->slot, c->cstart, c->tidx, c->tkey, np, c->mstride);
+              kBlock, 0, c->stream>>>(c->key, c->slot, c->cstart, c->tidx, np, c->mstride);
   LAUNCH_CHECK(c, "scatter");
   return PIC_OK;
 }
@@ -467,13 +467,13 @@ int order_particles(pic_ctx* c, bool bucketed) {
   const bool dep = c->fused;
   if (c->precision == PIC_FP64) {
     auto kfn = dep ? k_order_tiles<double, true> : k_order_tiles<double, false>;
-    kfn<<<G(c, ntiles), kTileThreads, 0, c->stream>>>(c->K, c->tile_c0, c->tile_s0, c->tidx, c->tkey,
+    kfn<<<G(c, ntiles), kTileThreads, 0, c->stream>>>(c->K, c->tile_c0, c->tile_s0, c->tidx,
                                                  c->cstart, c->x[s], c->v[s], c->sh[s], c->id[s],
                                                  c->x[d], c->v[d], c->sh[d], c->id[d], c->key,
                                                  (double*)c->mom, np, bucketed, c->flags);
   } else {
     auto kfn = dep ? k_order_tiles<float, true> : k_order_tiles<float, false>;
-    kfn<<<G(c, ntiles), kTileThreads, 0, c->stream>>>(c->K, c->tile_c0, c->tile_s0, c->tidx, c->tkey,
+    kfn<<<G(c, ntiles), kTileThreads, 0, c->stream>>>(c->K, c->tile_c0, c->tile_s0, c->tidx,
                                                  c->cstart, c->off[s], c->vf[s], c->asf[s],
                                                  c->id[s], c->off[d], c->vf[d], c->asf[d],
                                                  c->id[d], c->key, (float*)c->mom, np, bucketed, c->flags);

@@ -385,13 +385,12 @@ __global__ void __launch_bounds__(kBlock) k_scan_add(int* out, const int* bsum, 
 // kScatterPer particles per thread, loads issued before the dependent ones.
 constexpr int kScatterPer = 4;
 __global__ void __launch_bounds__(kBlock) k_scatter(const int* key, const int* slot,
-                                                    const int* cstart, int* tidx, int* tkey,
-                                                    int n, int64_t mstride) {
+                                                    const int* cstart, int* tidx, int n,
+                                                    int64_t mstride) {
   key = mem_z(mstride, key);
   slot = mem_z(mstride, slot);
   cstart = mem_z(mstride, cstart);
   tidx = mem_z(mstride, tidx);
-  tkey = mem_z(mstride, tkey);
   const int base = blockIdx.x * (kBlock * kScatterPer) + threadIdx.x;
   int k[kScatterPer], sl[kScatterPer];
 #pragma unroll
@@ -406,9 +405,7 @@ __global__ void __launch_bounds__(kBlock) k_scatter(const int* key, const int* s
   for (int q = 0; q < kScatterPer; ++q) {
     const int i = base + q * kBlock;
     if (i < n) {
-      const int dst = cstart[k[q]] + sl[q];
-      tidx[dst] = i;
-      tkey[dst] = k[q];
+      tidx[cstart[k[q]] + sl[q]] = i;
     }
   }
 }
@@ -420,11 +417,22 @@ __device__ inline int stable_rank(const int* tidx, int s, int e, int my) {
   return r;
 }
 
-// Destination of scatter slot j: its stable rank inside its cell, or (for a
-// cell beyond kMaxStableCell, flagged as a capacity error) the slot itself.
-__device__ inline int order_dst(const int* tidx, const int* tkey, const int* cstart, int j,
-                                int* flags) {
-  int c = tkey[j], s = cstart[c], e = cstart[c + 1];
+// Cell of scatter slot j among cells [c0, c1), whose starts are cs[0 ..]: the last
+// that starts at or before it.
+template <class I>
+__device__ inline int cell_of_slot(const I* cs, int c0, int c1, int j) {
+  int lo = c0, hi = c1;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if ((int)cs[mid - c0] <= j) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// Destination of scatter slot j of cell c: its stable rank inside the cell, or
+// (for a cell beyond kMaxStableCell, flagged as a capacity error) the slot itself.
+__device__ inline int order_dst(const int* tidx, const int* cstart, int c, int j, int* flags) {
+  int s = cstart[c], e = cstart[c + 1];
   if (e - s > kMaxStableCell) {
     atomicOr(&flags[kFlagCapacity], 1);
     return j;

@@ -12,9 +12,12 @@ namespace pic {
 // slot's rank among the source indices of its own cell, which is its place in
 // the stable order, is counted in LDS, and the particle's state moves from its
 // source to (cell start) + rank.  Same destinations as order_dst; tiles larger
-// than the LDS slots use order_dst itself.  Every global load a slot needs
-// (source index, cell, cell bounds, the state itself) is issued before the
-// block waits for the LDS copy, so a tile costs two dependent load rounds.
+// than the LDS slots use order_dst itself.  A slot's cell is found among the
+// tile's cell starts in LDS: written by the scatter beside the index and read
+// back here it was 8 bytes a particle (scatter and order 224 -> 216 us for 2^23
+// particles, FP64 320 -> 306).  Every global load a slot needs
+// (source index, the state itself) is issued before the block waits for
+// the LDS copies, so a tile costs two dependent load rounds.
 //
 // DEP: the same workgroup then deposits its tile: the eight cloud-in-cell
 // weights of each moved particle go to LDS at its sorted place, and one lane
@@ -25,7 +28,7 @@ namespace pic {
 template <class T, bool DEP>
 __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const int* tile_c0,
                                                               const int* tile_s0, const int* tidx,
-                                                              const int* tkey, const int* cstart,
+                                                              const int* cstart,
                                                               const T* xs, const T* vs,
                                                               const T* as, const int* ids, T* xd,
                                                               T* vd, T* ad, int* idd, int* keyd,
@@ -33,7 +36,6 @@ __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const 
   tile_c0 = mem(K, tile_c0);
   tile_s0 = mem(K, tile_s0);
   tidx = mem(K, tidx);
-  tkey = mem(K, tkey);
   cstart = mem(K, cstart);
   xs = mem(K, xs);
   vs = mem(K, vs);
@@ -47,15 +49,20 @@ __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const 
   mom = mem(K, mom);
   flags = mem(K, flags);
   constexpr int kPer = (kLdsSlots + kTileThreads - 1) / kTileThreads;
+  static_assert(kPer * kTileThreads > kLdsSlots && kLdsSlots < 65536, "every cell start is staged");
   __shared__ int lidx[kLdsSlots];
+  __shared__ unsigned short lcs[kLdsSlots + 1];  // (seven FP64 tiles fit a CU with it, not with int)
   __shared__ T W[DEP ? 8 * kLdsSlots : 1];
   const int s0 = tile_s0[blockIdx.x], ns = tile_s0[blockIdx.x + 1] - s0;
   if (ns <= 0) return;
+  // the tile's cells: the first cell of this tile up to the first of the next
+  const int c0 = min(tile_c0[blockIdx.x], K.nn);
+  const int c1 = min(max(tile_c0[blockIdx.x + 1], c0), K.nn);
   const bool lds = ns <= kLdsSlots;
   if (!lds) {
     for (int j = threadIdx.x; j < ns; j += kTileThreads) {
-      const int slot = s0 + j, my = tidx[slot];
-      const int dst = order_dst(tidx, tkey, cstart, slot, flags), src = bucketed ? slot : my;
+      const int slot = s0 + j, my = tidx[slot], c = cell_of_slot(cstart + c0, c0, c1, slot);
+      const int dst = order_dst(tidx, cstart, c, slot, flags), src = bucketed ? slot : my;
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         xd[(int64_t)d * n + dst] = xs[(int64_t)d * n + src];
@@ -63,29 +70,26 @@ __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const 
         ad[(int64_t)d * n + dst] = as[(int64_t)d * n + src];
       }
       idd[dst] = ids[src];
-      keyd[dst] = tkey[slot];
+      keyd[dst] = c;
     }
     if (!DEP) return;
     __threadfence_block();  // the tile's moved positions, read back below
     __syncthreads();
   } else {
-    int my[kPer], cc[kPer], cs[kPer], ce[kPer], idv[kPer];
+    int my[kPer], idv[kPer];
     T sv[kPer][9];
+    const bool few = c1 - c0 <= kLdsSlots;  // (else many are empty: their starts from memory)
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       const int j = threadIdx.x + q * kTileThreads;
-      if (j < ns) {
-        my[q] = tidx[s0 + j];
-        cc[q] = tkey[s0 + j];
-      }
+      if (j < ns) my[q] = tidx[s0 + j];
+      if (few && j <= c1 - c0) lcs[j] = (unsigned short)(cstart[c0 + j] - s0);
     }
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       const int j = threadIdx.x + q * kTileThreads;
       if (j < ns) {
         lidx[j] = my[q];
-        cs[q] = cstart[cc[q]] - s0;
-        ce[q] = cstart[cc[q] + 1] - s0;
         const int src = bucketed ? s0 + j : my[q];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
@@ -101,9 +105,12 @@ __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const 
     for (int q = 0; q < kPer; ++q) {
       const int j = threadIdx.x + q * kTileThreads;
       if (j < ns) {
+        const int c = few ? cell_of_slot(lcs, c0, c1, j) : cell_of_slot(cstart + c0, c0, c1, s0 + j);
+        const int cs = few ? lcs[c - c0] : cstart[c] - s0;
+        const int ce = few ? lcs[c - c0 + 1] : cstart[c + 1] - s0;
         int r = 0;
-        for (int k = cs[q]; k < ce[q]; ++k) r += lidx[k] < my[q];
-        const int dst = s0 + cs[q] + r;
+        for (int k = cs; k < ce; ++k) r += lidx[k] < my[q];
+        const int dst = s0 + cs + r;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
           xd[(int64_t)d * n + dst] = sv[q][d];
@@ -111,7 +118,7 @@ __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const 
           ad[(int64_t)d * n + dst] = sv[q][6 + d];
         }
         idd[dst] = idv[q];
-        keyd[dst] = cc[q];
+        keyd[dst] = c;
         if constexpr (DEP) {
           T w[8];
           if constexpr (std::is_same<T, float>::value) {
@@ -130,9 +137,6 @@ __global__ void __launch_bounds__(kTileThreads) k_order_tiles(SimConst K, const 
     __syncthreads();
   }
   if constexpr (DEP) {
-    // the tile's cells: the first cell of this tile up to the first of the next
-    const int c0 = min(tile_c0[blockIdx.x], K.nn);
-    const int c1 = min(max(tile_c0[blockIdx.x + 1], c0), K.nn);
     for (int l = threadIdx.x; l < 8 * (c1 - c0); l += kTileThreads) {
       const int k = l & 7, c = c0 + (l >> 3);
       const int a = cstart[c] - s0, e = cstart[c + 1] - s0;
