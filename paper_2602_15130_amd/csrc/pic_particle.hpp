@@ -193,8 +193,8 @@ __device__ inline void count_pairs(const PartArgs& a, unsigned long long acc, un
 }
 
 // Hands tile b to the general instance (thread 0; the caller returns uniformly).
-// The list is a count, dl[0], and the tiles from dl[1] on; the host clears the
-// count before every lean launch.
+// The list is a count, dl[0], and the tiles from dl[1] on; the scan of the sort
+// or the draw of the pairs has emptied it (else the host, before the launch).
 __device__ inline void defer_tile(const PartArgs& a, int b) {
   if (threadIdx.x == 0) {
     const int i = atomicAdd(&a.defer[0], 1);
