@@ -251,12 +251,14 @@ __global__ void __launch_bounds__(kBlock) k_count(const int* key, int* slot, int
 
 // Exclusive scan of n ints, 1024 items per block: the blocks by themselves, then
 // the sum of the blocks before each.  Up to kScanDirect blocks every workgroup
-// of the second pass adds those up itself (a launch of its own for them took 4.7
-// us, these loads under 1 us); their number grows with the square, so beyond
-// that one workgroup scans the block sums in between.
+// of the second pass adds those up itself; the number of these loads grows with
+// the square, so beyond that one workgroup scans the block sums in between.
+// Second pass alone against both launches, by blocks: 5 and 10 us (256), 15 and
+// 29 (4,000), 31 and 54 (7,800); by that growth about equal at 16,384, where both
+// launches take 107.
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kBlock * kScanItems;
-constexpr int kScanDirect = 2048;
+constexpr int kScanDirect = 8192;
 
 // Tile tables of the sort, filled before the last pass writes their bounds.
 struct TileInit {

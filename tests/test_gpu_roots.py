@@ -55,7 +55,8 @@ def test_initial_state_solves_its_cdfs(family):
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("nc,np_", [((3, 3, 3), 1), ((3, 4, 5), 300), ((3, 3, 3), 19001),
-                                    ((3, 3, 3), 70001), ((16, 16, 16), 4097), ((24, 24, 24), 1500)])
+                                    ((3, 3, 3), 70001), ((16, 16, 16), 4097), ((24, 24, 24), 1500),
+                                    ((128, 128, 129), 50001), ((204, 204, 204), 50001)])
 def test_initial_state_is_bucketed_and_ordered(nc, np_, precision):
     """Cells of every size (empty, one tile, larger than a tile's LDS slots): the
     particles of a cell in the order of their ids, each in its own cell, and
