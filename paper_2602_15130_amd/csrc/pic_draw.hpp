@@ -81,7 +81,8 @@ __global__ void __launch_bounds__(64 * kDrawWaves) k_draw_pairs(SimConst K, Part
       const int items = ncells * ngroups;
       for (int base = 0; base < (hi - lo) * items && !bad; base += 64) {
         const int l = base + lane;
-        const int li = lo + (l >= items ? 1 : 0), r = l - (li - lo) * items;
+        // (lanes past a single call's items stay on its list)
+        const int li = l >= items ? 1 : lo, r = l - (li - lo) * items;
         const int ci = r / ngroups, g = r - ci * ngroups;
         int np[4] = {0, 0, 0, 0}, cnt = 0, most = 0;
         if (l < (hi - lo) * items) {

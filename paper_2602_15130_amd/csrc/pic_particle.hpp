@@ -74,6 +74,8 @@ struct PairRec {
 enum { kPairsInTile = 0, kPairsDrawn = 1, kPairsChunks = 2 };
 constexpr int kRecCap = 128;       // records of one call that a tile may have (record instances)
 constexpr unsigned kNoSlot = 0xffffu;
+static_assert(kRecCap <= kTileThreads, "a thread per record of a list");
+static_assert(kLdsSlots < (int)kNoSlot, "a tile's slots are told from no slot");
 // Velocity changes of the pairs held at once: two per pair (entries 2 r and 2 r + 1
 // belong to pair r, an outcome fills its pairs' entries from the front).
 template <class R, int PAIRS>
@@ -91,6 +93,7 @@ struct CellRanges {
 // LDS of a call that draws and applies its pairs in chunks (tile_dense).
 constexpr int kDenseChunk = 256;   // pairs of a chunk, one per thread
 constexpr int kDenseMaxPairs = 64; // pairs of an outcome at most
+static_assert(kDenseChunk == kTileThreads, "a thread per pair of a chunk");
 template <class R>
 struct DenseLds {
   PairLds<R, kDenseChunk> P;
