@@ -160,16 +160,19 @@ int validate(const pic_problem* p, const pic_discretization* d, int precision, s
 
 int grid_for(int64_t n) { return (int)std::max<int64_t>(1, (n + kBlock - 1) / kBlock); }
 
-// Instances of the brick solver: nodes per thread and threads per workgroup.
+// Instances of the brick solver: nodes per thread and threads per workgroup;
+// the plain one and the one launched after a direct solve.
 struct BrickKernel {
   int q, nt;
-  const void* fn;
+  const void* fn[2];
 };
+template <int Q, int NT>
+BrickKernel brick_kernel() {
+  return {Q, NT, {(const void*)k_cg_brick<Q, NT, false>, (const void*)k_cg_brick<Q, NT, true>}};
+}
 const BrickKernel kBrickKernels[] = {
-    {1, 256, (const void*)k_cg_brick<1, 256>},   {2, 256, (const void*)k_cg_brick<2, 256>},
-    {4, 256, (const void*)k_cg_brick<4, 256>},   {8, 256, (const void*)k_cg_brick<8, 256>},
-    {16, 256, (const void*)k_cg_brick<16, 256>}, {16, 512, (const void*)k_cg_brick<16, 512>},
-    {8, 1024, (const void*)k_cg_brick<8, 1024>},  {4, 1024, (const void*)k_cg_brick<4, 1024>},
+    brick_kernel<1, 256>(),  brick_kernel<2, 256>(),  brick_kernel<4, 256>(),  brick_kernel<8, 256>(),
+    brick_kernel<16, 256>(), brick_kernel<16, 512>(), brick_kernel<8, 1024>(), brick_kernel<4, 1024>(),
 };
 constexpr int kNumBrickKernels = sizeof(kBrickKernels) / sizeof(kBrickKernels[0]);
 
@@ -1297,12 +1300,21 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
   c->nrec = carve<int>(c, A_NREC);
   c->spread = carve<unsigned long long>(c, A_SPREAD);
 
+  // The direct solve takes the place of the low-mode pre-solve unless the
+  // caller asked for a number of modes, or allows fewer CG iterations than the
+  // pre-solved CG may need (a call that is refused for that stays refused:
+  // 4 n covers it, 29 iterations at 128^3), or wants the residual below 1e-15 of
+  // the right-hand side, where rounding decides whether any solver gets there.
+  c->direct = !std::getenv("PIC_CG_LOWMODES") && c->cg_tol >= 1e-15 &&
+              c->cg_max_iter >= 4 * std::max({c->K.nc[0], c->K.nc[1], c->K.nc[2]});
+
   // Cooperative grid for the Poisson solver: one block per CU at most, never
   // more than the node count needs, and never more than can be co-resident.
+  const void* cg_global = c->direct ? (const void*)k_cg<true> : (const void*)k_cg<false>;
   int dev = 0, ncu = 1, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_cg, kBlock, 0);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cg_global, kBlock, 0);
   if (e != hipSuccess || per_cu < 1) {
     g_create_error = std::string("device query failed: ") + hipGetErrorString(e);
     delete c;
@@ -1326,7 +1338,7 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
       c->cg_grid = std::min(c->cg_grid, want);
     }
   }
-  c->cg_fn = (const void*)k_cg;
+  c->cg_fn = cg_global;
   c->cg_nt = kBlock;
   const char* force_global = std::getenv("PIC_CG_GLOBAL");
   // (the brick solver's on-chip stencil is the 7-point one)
@@ -1344,28 +1356,29 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     for (int ki = 0; ki < kNumBrickKernels; ++ki) {
       per[ki] = 0;
       if (only_q && (kBrickKernels[ki].q != only_q || kBrickKernels[ki].nt != only_nt)) continue;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per[ki], kBrickKernels[ki].fn,
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per[ki], kBrickKernels[ki].fn[c->direct],
                                                        kBrickKernels[ki].nt, 0) != hipSuccess)
         per[ki] = 0;
     }
     BrickChoice bc{};
     if (choose_bricks(c->K.nc, per, ncu, (size_t)lds_max, std::min(target, ncu), bc)) {
       const BrickKernel& bk = kBrickKernels[bc.kernel];
+      const void* fn = bk.fn[c->direct];
       const size_t lds = brick_lds_bytes(bc.bd);
       const int grid = bc.nbr[0] * bc.nbr[1] * bc.nbr[2];
       bool ok = true;
       if (lds > 65536)
-        ok = hipFuncSetAttribute(bk.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) ==
+        ok = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) ==
              hipSuccess;
       // the chosen instance must be co-resident at this grid with its LDS
       int occ = 0;
-      if (ok && (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, bk.fn, bk.nt, lds) != hipSuccess ||
+      if (ok && (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, bk.nt, lds) != hipSuccess ||
                  (int64_t)occ * ncu < grid))
         ok = false;
       if (ok) {
         c->cg_q = bk.q;
         c->cg_nt = bk.nt;
-        c->cg_fn = bk.fn;
+        c->cg_fn = fn;
         for (int d = 0; d < 3; ++d) {
           c->cg_bd[d] = bc.bd[d];
           c->cg_nbr[d] = bc.nbr[d];
@@ -1425,15 +1438,9 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     }
   }
 
-  // The direct solve takes the place of the low-mode pre-solve unless the
-  // caller asked for a number of modes, or allows fewer CG iterations than the
-  // pre-solved CG may need (a call that is refused for that stays refused:
-  // 4 n covers it, 29 iterations at 128^3), or wants the residual below 1e-15 of
-  // the right-hand side, where rounding decides whether any solver gets there.
   {
     const int* nc = c->K.nc;
     const int nmax = std::max({nc[0], nc[1], nc[2]});
-    c->direct = !std::getenv("PIC_CG_LOWMODES") && c->cg_max_iter >= 4 * nmax && c->cg_tol >= 1e-15;
     DirectArgs& D = c->dir;
     double* p = carve<double>(c, A_DIRECT);
     for (int d = 0; d < 3; ++d) {

@@ -146,7 +146,7 @@ inline size_t brick_lds_bytes(const int bd[3]) {
 // owns the column (li, lj) = (t mod bdim[0], t / bdim[0]) and its nodes
 // lk = 0..Q-1, so its node q sits at padded index pl0 + q pxy and mesh node
 // gn0 + q nx ny (a brick never wraps inside).
-template <int Q, int NT>
+template <int Q, int NT, bool AFTER>
 __device__ __attribute__((always_inline)) inline void cg_brick_solve(const SimConst& K, const CgArgs& a,
                                                                      double* R, double* sh) {
   const int bd[3] = {a.bdim[0], a.bdim[1], Q};
@@ -321,17 +321,25 @@ __device__ __attribute__((always_inline)) inline void cg_brick_solve(const SimCo
     *a.iters_out = it;
     *a.relres_out = bnorm == 0.0 ? 0.0 : sqrt(gamma) / bnorm;
   }
-  cg_rebuild_field<NT>(K, a, ++gen, sh);
+  if constexpr (AFTER) cg_rebuild_field<NT>(K, a, ++gen, sh);
 }
 
-template <int Q, int NT>
+// AFTER: the instance launched after a direct solve.  (One instance for both
+// kept its registers over the loop of members: 393 against 233 of a lane's
+// spilled with 512 threads and 16 nodes each, and a step of a 96^3 mesh solved
+// by the CG took 890 us in place of 626.)
+template <int Q, int NT, bool AFTER>
 __global__ void __launch_bounds__(NT) k_cg_brick(SimConst K, CgArgs a0) {
   extern __shared__ double R[];
   __shared__ double sh[3 * (NT / 64)];
-  for (int m = 0; m < a0.members; ++m, ++K.member0) {
-    const CgArgs a = member_view(K, a0);
-    if (!direct_converged<NT>(a, sh)) cg_brick_solve<Q, NT>(K, a, R, sh);
-    __syncthreads();  // before the next member's solve reuses the LDS
+  if constexpr (!AFTER) {
+    cg_brick_solve<Q, NT, AFTER>(K, member_view(K, a0), R, sh);
+  } else {
+    for (int m = 0; m < a0.members; ++m) {
+      const CgArgs a = member_view(K, a0, m);
+      if (!direct_converged<NT>(a, sh)) cg_brick_solve<Q, NT, AFTER>(K, a, R, sh);
+      __syncthreads();  // before the next member's solve reuses the LDS
+    }
   }
 }
 

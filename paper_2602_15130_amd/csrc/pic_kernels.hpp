@@ -2,6 +2,8 @@
 // mixed form (sort, scan, Poisson CG, gradient, norms).
 #pragma once
 
+#include <type_traits>
+
 #include "pic_device.hpp"
 
 namespace pic {
@@ -747,27 +749,15 @@ __device__ inline bool spin_until(const unsigned* addr, unsigned want, int* flag
   return true;
 }
 
-// The solver's arrays of one ensemble member.
-__device__ inline CgArgs member_view(const SimConst& K, CgArgs a) {
-  a.b = mem(K, a.b);
-  a.x = mem(K, a.x);
-  for (int i = 0; i < 2; ++i) {
-    a.r[i] = mem(K, a.r[i]);
-    a.w[i] = mem(K, a.w[i]);
-    a.s[i] = mem(K, a.s[i]);
-  }
-  a.p = mem(K, a.p);
-  a.part = mem(K, a.part);
-  a.result = mem(K, a.result);
-  a.arrive = mem(K, a.arrive);
-  a.release = mem(K, a.release);
-  a.flags = mem(K, a.flags);
-  a.iters_out = mem(K, a.iters_out);
-  a.relres_out = mem(K, a.relres_out);
-  a.pub = mem(K, a.pub);
-  a.check = mem(K, a.check);
-  a.E = mem(K, a.E);
-  a.E32 = mem(K, a.E32);
+// The solver's arrays of the workgroup's ensemble member, or of the m-th after it.
+__device__ inline CgArgs member_view(const SimConst& K, CgArgs a, int m = 0) {
+  const int64_t shift = ((int64_t)member_of(K) + m) * K.mstride;
+  auto at = [&](auto*& p) {
+    if (p) p = (std::remove_reference_t<decltype(p)>)((char*)p + shift);
+  };
+  at(a.b), at(a.x), at(a.p), at(a.part), at(a.result), at(a.arrive), at(a.release), at(a.flags);
+  at(a.iters_out), at(a.relres_out), at(a.pub), at(a.check), at(a.E), at(a.E32);
+  for (int i = 0; i < 2; ++i) at(a.r[i]), at(a.w[i]), at(a.s[i]);
   return a;
 }
 
@@ -881,7 +871,6 @@ __device__ inline void warm_residual(const SimConst& K, int n, int i, int j, int
 // same sums in the same order in every workgroup).
 template <int NT>
 __device__ inline bool direct_converged(const CgArgs& a, double* sh) {
-  if (a.ncheck <= 0) return false;
   double v[kMaxRed] = {0.0, 0.0, 0.0};
   for (int i = threadIdx.x; i < a.ncheck; i += NT) {
     v[0] += a.check[i];
@@ -900,7 +889,6 @@ __device__ inline bool direct_converged(const CgArgs& a, double* sh) {
 // E from the potential that the CG left, after a direct solve that fell short.
 template <int NT>
 __device__ inline void cg_rebuild_field(const SimConst& K, const CgArgs& a, unsigned gen, double* sh) {
-  if (a.ncheck <= 0) return;
   double z[kMaxRed] = {0.0, 0.0, 0.0};
   if (!grid_sum_t<NT>(a, z, 1, gen, sh)) return;  // every workgroup's part of x is visible
   for (int n = blockIdx.x * NT + threadIdx.x; n < K.nn; n += gridDim.x * NT) {
@@ -910,6 +898,7 @@ __device__ inline void cg_rebuild_field(const SimConst& K, const CgArgs& a, unsi
   }
 }
 
+template <bool AFTER>
 __device__ inline void cg_solve(const SimConst& K, const CgArgs& a, double* sh) {
   const int gsize = gridDim.x * kBlock;
   const int g0 = blockIdx.x * kBlock + threadIdx.x;
@@ -997,14 +986,20 @@ __device__ inline void cg_solve(const SimConst& K, const CgArgs& a, double* sh) 
     *a.iters_out = it;
     *a.relres_out = bnorm == 0.0 ? 0.0 : sqrt(gamma) / bnorm;
   }
-  cg_rebuild_field<kBlock>(K, a, ++gen, sh);
+  if constexpr (AFTER) cg_rebuild_field<kBlock>(K, a, ++gen, sh);
 }
 
+// AFTER: the instance launched after a direct solve.
+template <bool AFTER>
 __global__ void __launch_bounds__(kBlock) k_cg(SimConst K, CgArgs a0) {
   __shared__ double sh[3 * kWaves];
-  for (int m = 0; m < a0.members; ++m, ++K.member0) {
-    const CgArgs a = member_view(K, a0);
-    if (!direct_converged<kBlock>(a, sh)) cg_solve(K, a, sh);
+  if constexpr (!AFTER) {
+    cg_solve<AFTER>(K, member_view(K, a0), sh);
+  } else {
+    for (int m = 0; m < a0.members; ++m) {
+      const CgArgs a = member_view(K, a0, m);
+      if (!direct_converged<kBlock>(a, sh)) cg_solve<AFTER>(K, a, sh);
+    }
   }
 }
 
