@@ -1111,12 +1111,13 @@ int errors_into(pic_ctx* c, pic_error_norms* out, double* epart, double* npart, 
   const int nbp = err_grid(K.np), nbn = err_grid(K.nn);
   int s = c->cur;
   if (c->precision == PIC_FP64) {
-    k_err_particles_f64<<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->x[s], c->v[s], c->sh[s],
-                                                             c->id[s], epart, c->flags);
+    k_err_positions_f64<<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->x[s], c->id[s], epart, c->flags);
+    (K.family == 1 ? k_err_velocities<true, double> : k_err_velocities<false, double>)
+        <<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->v[s], c->id[s], epart, c->flags);
   } else {
     k_err_positions_mixed<<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->key, c->off[s], c->id[s],
                                                                epart, c->flags);
-    (K.family == 1 ? k_err_velocities_mixed<true> : k_err_velocities_mixed<false>)
+    (K.family == 1 ? k_err_velocities<true, float> : k_err_velocities<false, float>)
         <<<G(c, nbp), kBlock, 0, c->stream>>>(K, t, c->vf[s], c->id[s], epart, c->flags);
   }
   k_err_nodes<<<G(c, nbn), kBlock, 0, c->stream>>>(K, t, c->phi, npart);

@@ -1362,35 +1362,57 @@ __device__ inline void err_row(const double* s2, const double* mx, double* part,
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_err_particles_f64(SimConst K, double t,
-                                                              const double* x, const double* v,
-                                                              const double* ash, const int* id,
-                                                              double* part, int* flags) {
+// Positions and velocities apart, both against the manufactured state of the
+// particle's identity.  Bound by the FP64 instructions of the roots, whose
+// polynomial constants stay in registers over the loop: in one kernel those of
+// both filled the 256 of a thread (one wave per SIMD).  2^23 particles in the
+// mixed form: 1307 us -> 200 + 415 (configuration family), 8780 -> 295 + 810
+// (paper's).
+__global__ void __launch_bounds__(kBlock) k_err_positions_f64(SimConst K, double t, const double* x,
+                                                              const int* id, double* part, int* flags) {
   x = mem(K, x);
-  v = mem(K, v);
-  ash = mem(K, ash);
   id = mem(K, id);
   part = mem(K, part);
   flags = mem(K, flags);
   __shared__ double sh[kWaves];
-  double s2[6] = {0, 0, 0, 0, 0, 0}, mx[6] = {0, 0, 0, 0, 0, 0};
+  double s2[3] = {0, 0, 0}, mx[3] = {0, 0, 0};
   bool bad = false;
   const PaperTime P = paper_time(K, t);
   for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < K.np;
        i += (int64_t)gridDim.x * kBlock) {
-    double xq[3], xm[3], vm[3], vd[3];
+    double xq[3], xm[3];
     position_uniforms(K, id[i], xq);
     const double xp[3] = {x[i], x[K.np + i], x[2 * K.np + i]};
     manufactured_position(K, xq, P, xp, xm);
-    const double a[3] = {ash[i], ash[K.np + i], ash[2 * K.np + i]};
-    manufactured_velocity(K, a, t, vm, vd);
-    for (int d = 0; d < 3; ++d) {
-      err_add(wrapped_error(xp[d] - xm[d], K.L[d]), s2[d], mx[d], bad);
-      err_add(v[d * K.np + i] - vm[d], s2[3 + d], mx[3 + d], bad);
-    }
+    for (int d = 0; d < 3; ++d) err_add(wrapped_error(xp[d] - xm[d], K.L[d]), s2[d], mx[d], bad);
   }
   if (bad) atomicOr(&flags[kFlagNonFinite], 1);
-  err_row<6>(s2, mx, part, 0, sh);
+  err_row<3>(s2, mx, part, 0, sh);
+}
+
+// (The velocity shape comes from the identity's uniforms, not from the shape
+// that the state carries: an error that moved both the velocity and its shape
+// to another identity would not show against that.)
+template <bool CFG, class R>  // CFG: the configuration family's normal velocities, else Sec. 5.2's
+__global__ void __launch_bounds__(kBlock) k_err_velocities(SimConst K, double t, const R* v,
+                                                           const int* id, double* part, int* flags) {
+  v = mem(K, v);
+  id = mem(K, id);
+  part = mem(K, part);
+  flags = mem(K, flags);
+  __shared__ double sh[kWaves];
+  double s2[3] = {0, 0, 0}, mx[3] = {0, 0, 0};
+  bool bad = false;
+  for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < K.np;
+       i += (int64_t)gridDim.x * kBlock) {
+    double xv[3], a[3], vm[3], vd[3];
+    velocity_uniforms(K, id[i], xv);
+    for (int d = 0; d < 3; ++d) a[d] = CFG ? normal_quantile(xv[d]) : paper_a(xv[d]);
+    manufactured_velocity(K, a, t, vm, vd);
+    for (int d = 0; d < 3; ++d) err_add((double)v[d * K.np + i] - vm[d], s2[d], mx[d], bad);
+  }
+  if (bad) atomicOr(&flags[kFlagNonFinite], 1);
+  err_row<3>(s2, mx, part, 3, sh);
 }
 
 // What a query of the state checks, over all members of an ensemble.

@@ -701,13 +701,9 @@ __global__ void __launch_bounds__(kBlock) k_export_mixed(SimConst K, const int* 
   }
 }
 
-// Error norms of the mixed state: positions rebuilt in FP64, manufactured
+// Error norms of the mixed state's positions: rebuilt in FP64, manufactured
 // values from FP64 roots, FP64 reductions (same fixed grid and order as
-// k_err_particles_f64).  Bound by the FP64 instructions of the roots; positions
-// and velocities apart, for the roots' polynomial constants stay in registers
-// over the loop and in one kernel those of both filled the 256 of a thread (one
-// wave per SIMD).  2^23 particles: 1307 us -> 200 + 415 (configuration
-// family), 8780 -> 295 + 810 (paper's).
+// k_err_positions_f64).
 __global__ void __launch_bounds__(kBlock) k_err_positions_mixed(SimConst K, double t, const int* key,
                                                                 const float* off, const int* id,
                                                                 double* part, int* flags) {
@@ -732,29 +728,6 @@ __global__ void __launch_bounds__(kBlock) k_err_positions_mixed(SimConst K, doub
   }
   if (bad) atomicOr(&flags[kFlagNonFinite], 1);
   err_row<3>(s2, mx, part, 0, sh);
-}
-
-template <bool CFG>  // the configuration family's normal velocities, else Sec. 5.2's
-__global__ void __launch_bounds__(kBlock) k_err_velocities_mixed(SimConst K, double t, const float* vf,
-                                                                 const int* id, double* part,
-                                                                 int* flags) {
-  vf = mem(K, vf);
-  id = mem(K, id);
-  part = mem(K, part);
-  flags = mem(K, flags);
-  __shared__ double sh[kWaves];
-  double s2[3] = {0, 0, 0}, mx[3] = {0, 0, 0};
-  bool bad = false;
-  for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < K.np;
-       i += (int64_t)gridDim.x * kBlock) {
-    double xv[3], a[3], vm[3], vd[3];
-    velocity_uniforms(K, id[i], xv);
-    for (int d = 0; d < 3; ++d) a[d] = CFG ? normal_quantile(xv[d]) : paper_a(xv[d]);
-    manufactured_velocity(K, a, t, vm, vd);
-    for (int d = 0; d < 3; ++d) err_add((double)vf[d * K.np + i] - vm[d], s2[d], mx[d], bad);
-  }
-  if (bad) atomicOr(&flags[kFlagNonFinite], 1);
-  err_row<3>(s2, mx, part, 3, sh);
 }
 
 }  // namespace pic
