@@ -345,7 +345,9 @@ __global__ void __launch_bounds__(kBlock) k_scan_blocks(int* bsum, int nb, int* 
 // tiles, tile_c0[t] = min{c : cstart[c] >= t kTileB} and tile_s0[t] =
 // cstart[tile_c0[t]]: with lo = cstart[j] and hi = cstart[j + 1] = lo + count[j],
 // cell c = j + 1 is that minimum for every t with lo < t kTileB <= hi.  Tile 0
-// starts at cell 0; tiles past the end keep the fill of pass 1.
+// starts at cell 0; the end of the last tile keeps the fill of pass 1, all cells,
+// so that the empty cells after the last particle belong to it (their moments
+// are written with the others').
 __global__ void __launch_bounds__(kBlock) k_scan_add(int* out, const int* bsum, int scanned, int n,
                                                      int* count, TileInit ti, int64_t mstride) {
   out = mem_z(mstride, out);
@@ -374,7 +376,7 @@ __global__ void __launch_bounds__(kBlock) k_scan_add(int* out, const int* bsum, 
     const int lo = out[jj] + add, hi = lo + count[jj];
     out[jj] = lo;
     count[jj] = 0;
-    for (int t = lo / kTileB + 1; t * kTileB <= hi && t <= ti.ntiles; ++t) {
+    for (int t = lo / kTileB + 1; t < ti.ntiles && t * kTileB <= hi; ++t) {
       ti.c0[t] = jj + 1;
       ti.s0[t] = hi;
     }
