@@ -832,12 +832,16 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
   ag.defer_list = full ? 0 : 1;
   const dim3 grid_last = G(c, full ? tiles : std::min(tiles, kDeferGrid));
   if (!full && first == 2 && (K.collisions || (a.mode & kCollideOnly))) {
+    const bool by_tile =
+        draw_by_tile((int64_t)tiles * c->members, (int64_t)K.nn * ((K.navg + 3) / 4) / tiles);
     const int per = draw_tiles_per_wave((int64_t)tiles * c->members);
-    const dim3 gd = G(c, (unsigned)((tiles + kDrawWaves * per - 1) / (kDrawWaves * per)));
+    const dim3 gd = G(c, by_tile ? tiles : (unsigned)((tiles + kDrawWaves * per - 1) / (kDrawWaves * per)));
     if (c->precision == PIC_MIXED)
-      k_draw_pairs<float><<<gd, 64 * kDrawWaves, 0, c->stream>>>(K, a, per);
+      by_tile ? k_draw_tile<float><<<gd, 64 * kDrawWaves, 0, c->stream>>>(K, a)
+              : k_draw_pairs<float><<<gd, 64 * kDrawWaves, 0, c->stream>>>(K, a, per);
     else
-      k_draw_pairs<double><<<gd, 64 * kDrawWaves, 0, c->stream>>>(K, a, per);
+      by_tile ? k_draw_tile<double><<<gd, 64 * kDrawWaves, 0, c->stream>>>(K, a)
+              : k_draw_pairs<double><<<gd, 64 * kDrawWaves, 0, c->stream>>>(K, a, per);
     LAUNCH_CHECK(c, "draw pairs");
     c->defer_empty = true;
   }

@@ -1,6 +1,6 @@
 // Test harness: the kernels that the library launches for the collisions of a
-// pass, run on the CPU under the workgroup emulator (emu.hpp): k_draw_pairs and
-// the instance that takes its lists, the instance that draws its pairs in chunks,
+// pass, run on the CPU under the workgroup emulator (emu.hpp): k_draw_pairs or
+// k_draw_tile and the instance that takes their lists, the instance that draws its pairs in chunks,
 // each followed by the general instance over the tiles it left, the general
 // instance alone, and k_collide_heavy beside the serial k_collide_f64.
 // A fence of one wave is a barrier of that wave here: on the GPU its lanes run in
@@ -40,7 +40,7 @@ unsigned long long heavy_acc[3 * kHeavyMaxLdsN];  // the launch's dynamic LDS
 }
 using namespace pic;
 
-enum Source { kGeneral = 0, kDrawn = 1, kChunks = 2, kHeavy = 3, kSerial = 4 };
+enum Source { kGeneral = 0, kDrawn = 1, kChunks = 2, kHeavy = 3, kSerial = 4, kDrawnByTile = 5 };
 
 struct Header {
   uint64_t seed, rng_seed;
@@ -84,13 +84,16 @@ static void run_pass(const SimConst& K, PartArgs a, const Header& h, std::mt1993
   };
   if (h.source == kGeneral) return sweep(0, (unsigned)a.ntiles, a);
   a.defer[0] = 0;
+  const bool drawn = h.source != kChunks;
+  if (drawn) a.defer[0] = 99;  // (the draw empties the list)
+  if (h.source == kDrawnByTile)
+    run_grid2((unsigned)a.ntiles, 1, 64 * kDrawWaves, [&] { k_draw_tile<R>(K, a); }, h.order, rng);
   if (h.source == kDrawn) {
-    a.defer[0] = 99;  // (the draw empties the list)
     const int per = h.order == emu::kForward ? 1 : kDrawTiles;
     run_grid2((unsigned)((a.ntiles + kDrawWaves * per - 1) / (kDrawWaves * per)), 1, 64 * kDrawWaves,
               [&] { k_draw_pairs<R>(K, a, per); }, h.order, rng);
   }
-  sweep(h.source == kDrawn ? 1 : 2, (unsigned)a.ntiles, a);
+  sweep(drawn ? 1 : 2, (unsigned)a.ntiles, a);
   a.defer_list = 1;
   sweep(0, (unsigned)std::min(a.ntiles, 7), a);
 }
@@ -198,7 +201,7 @@ int main(int argc, char** argv) {
   MembersAny any{};
   std::mt19937_64 rng(h.rng_seed);
   int left = 0, rc = 0;
-  if (h.source >= kHeavy) {  // one FP64 collision call
+  if (h.source == kHeavy || h.source == kSerial) {  // one FP64 collision call
     if (h.source == kSerial) {
       emu::run_grid((unsigned)((nn + kBlock - 1) / kBlock), kBlock, [&] {
         k_collide_f64(K, 0, h.step, v.data(), cs.data(), out.data(), gu.data(), nullptr, 0,

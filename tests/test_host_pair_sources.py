@@ -21,7 +21,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 EMU = os.path.join(ROOT, "tests", "host_emu")
 CSRC = os.path.join(ROOT, "paper_2602_15130_amd", "csrc")
 FORWARD, REVERSE, SHUFFLE = ORDERS = 0, 1, 2
-GENERAL, DRAWN, CHUNKS, HEAVY, SERIAL = range(5)
+GENERAL, DRAWN, CHUNKS, HEAVY, SERIAL, DRAWN_BY_TILE = range(6)
 DO_B, DO_A, COLLIDE_ONLY = 1, 2, 4
 
 
@@ -43,17 +43,27 @@ def harness(tmp_path_factory):
     return exe, d
 
 
+_states = {}
+
+
+def _oracle_state(prob, disc, steps):
+    at = (id(prob), steps)
+    if at not in _states:
+        o = O.Sim(prob, disc, 5, 0)
+        assert o.init() == 0 and o.step(steps) == 0
+        cs = o.get(o.CELL_START).astype(np.int32)
+        key = np.repeat(np.arange(len(cs) - 1, dtype=np.int32), np.diff(cs))
+        _states[at] = b"".join(a.tobytes() for a in (
+            o.get(o.V), cs, key, o.get(o.X), o.get(o.ID).astype(np.int32), o.get(o.E)))
+    return _states[at]
+
+
 def _run(harness, prob, disc, source, mode, order, precision=0, steps=1, lds_n=1920, split=1):
     from paper_2602_15130_amd import pic as P
     exe, d = harness
-    o = O.Sim(prob, disc, 5, 0)
-    assert o.init() == 0 and o.step(steps) == 0
-    cs = o.get(o.CELL_START).astype(np.int32)
-    key = np.repeat(np.arange(len(cs) - 1, dtype=np.int32), np.diff(cs))
     blob = bytes(P.make_problem(prob)) + bytes(P.make_disc(disc))
     blob += struct.pack("<QQqiiiiii", 5, 11, steps, precision, order, source, mode, lds_n, split)
-    for a in (o.get(o.V), cs, key, o.get(o.X), o.get(o.ID).astype(np.int32), o.get(o.E)):
-        blob += a.tobytes()
+    blob += _oracle_state(prob, disc, steps)
     (d / "in.bin").write_bytes(blob)
     r = subprocess.run([exe, str(d / "in.bin"), str(d / "out.bin")], capture_output=True, text=True,
                        timeout=600)
@@ -86,6 +96,7 @@ def _paper(navg):
 
 # mesh, particles per cell, pairs per outcome, outcomes
 CASES = {"few": _cfg((4, 4, 4), 32, 0.06, 16),
+         "many_outcomes": _cfg((3, 3, 4), 20, 0.02, 203),
          "ragged": _cfg((7, 5, 6), 3, 0.4, 6),       # N_avg no multiple of four, some empty cells
          "over_four": _cfg((4, 4, 4), 40, 4.2, 3),   # outcomes of more pairs than a list takes
          "overflow": _cfg((4, 3, 4), 32, 0.9, 20),   # lists that overflow
@@ -110,12 +121,12 @@ def test_pair_sources_agree_in_every_order(harness, case, precision):
         # the whole pass in several orders, the others in one
         whole = ORDERS if case in ("few", "chunks") else (REVERSE, SHUFFLE)
         for order in whole if mode == DO_B | DO_A else (SHUFFLE,):
-            for source in (DRAWN, CHUNKS):
+            for source in (DRAWN, DRAWN_BY_TILE, CHUNKS):
                 got = _run(harness, prob, disc, source, mode, order, precision)
                 assert _same(got, ref), (mode, order, source)
-                if case in ("large_cells", "over_64") or (case == "overflow" and source == DRAWN):
+                if case in ("large_cells", "over_64") or (case == "overflow" and source != CHUNKS):
                     assert got["left"] > 0
-                if case in ("few", "chunks") and source == CHUNKS or (case == "few" and source == DRAWN):
+                if case in ("few", "many_outcomes") or (case == "chunks" and source == CHUNKS):
                     assert got["left"] == 0
 
 
