@@ -272,6 +272,7 @@ struct pic_ctx {
   float* Df{};
   bool fused = true;
   bool lean_pass = true;        // lean pass instance first, general one for the tiles it defers
+  bool scan_events = false;     // mixed event lists are scanned, never sorted
   // Captured steps (pic_use_graphs): two steps per graph, one graph per
   // double-buffer parity, recorded on a private stream and replayed on the
   // context's stream; kernels then take the step from *stepc.
@@ -747,6 +748,7 @@ PartArgs part_args(pic_ctx* c) {
   a.mixc = c->mixc;
   a.ntiles = (int)((c->K.np + kTileB - 1) / kTileB);
   a.defer_list = 0;
+  a.scan_events = c->scan_events;
   a.callB = 1;
   a.callA = 0;
   return a;
@@ -1245,6 +1247,9 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     const double need = pairs * (double)c->K.navg * ((double)kTileB / std::max(nbar, 1.0));
     c->lean_pass = !c->K.collisions || need <= 0.5 * kRecCap;
     if (const char* lp = std::getenv("PIC_LEAN_PASS")) c->lean_pass = lp[0] == '1';
+    // PIC_SORT_EVENTS=0: the mixed form's event lists (the full and the general
+    // instance) are scanned however long they are.
+    if (const char* se = std::getenv("PIC_SORT_EVENTS")) c->scan_events = se[0] != '1';
   }
   c->cg_tol = disc->cg_tol;
   c->cg_max_iter = disc->cg_max_iter;

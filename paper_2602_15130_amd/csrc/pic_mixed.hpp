@@ -486,7 +486,7 @@ __global__ void __launch_bounds__(kTileThreads, PAIRS == kPairsDrawn    ? PIC_MI
             return;
           }
         }
-        tile_run<SIG, float, FULL, FAST, true>(K, a, li, call, step, c0, ncells, s0, ns, v0, u, D, mark,
+        tile_run<SIG, float, FULL, FAST>(K, a, li, call, step, c0, ncells, s0, ns, v0, u, D, mark,
                                                tl, li ? K.navg : 0, st, NP, cl,
                                                few_cells ? lcs : nullptr);
       }

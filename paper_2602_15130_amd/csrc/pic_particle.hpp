@@ -134,6 +134,7 @@ struct PartArgs {
   // the list when defer_list is set, else through all tiles
   int* defer;
   int ntiles, defer_list;
+  int scan_events;  // the mixed form's event lists are never sorted
   // pairs drawn before the pass (record instances): call B's and call A's, [ntiles][kRecCap]
   // of PairRec, and their numbers [ntiles][2] (-1: the tile does not fit)
   void *recB, *recA;
@@ -666,21 +667,21 @@ __device__ __attribute__((always_inline)) inline void tile_dense(const SimConst&
   __syncthreads();
 }
 
+// Whether a call's event list is sorted for the cell threads: always in the
+// FP64 pass; in the mixed pass from kSortEvents events on (with few the plain scan
+// is faster), and not at all with scan_events.
+constexpr int kSortEvents = 24;
+template <class R>
+__device__ inline bool sorted_list(const PartArgs& a, int ne) {
+  return sizeof(R) == 8 || (ne > kSortEvents && !a.scan_events);
+}
+
 // The outcomes of one cell that have candidate pairs, in increasing outcome
 // order, summed into D (eq. avg_outcome; the division by N_avg is done where D
 // is read).  Outcomes already run by a lane contribute their stored changes;
 // the others run here.  Only the particles an outcome changed contribute to
 // the sum; the others would add exact zeros.
-// Whether a call's event list is sorted for the cell threads: always in the
-// FP64 pass; in the mixed pass (SORT instances, launched where a tile's lists
-// are expected to be long) from kSortEvents events on.  With few events the
-// mixed pass is faster with the plain scan, and faster still in instances
-// compiled without the sort at all.
-constexpr int kSortEvents = 24;
-template <class R, bool SORT>
-__device__ inline bool sorted_list(int ne) { return sizeof(R) == 8 || (SORT && ne > kSortEvents); }
-
-template <int SIG, class R, bool FULL, bool LANE_ONLY, bool SORT, class Lds>
+template <int SIG, class R, bool FULL, bool LANE_ONLY, class Lds>
 __device__ __attribute__((always_inline)) inline void cell_outcomes(const SimConst& K, const PartArgs& a, int call, int64_t step,
                                      int c, int ci, int cs, int n, const R* v0, R* u, R* D,
                                      int* mark, int* tl, int tagbase, int st, int stu,
@@ -693,7 +694,7 @@ __device__ __attribute__((always_inline)) inline void cell_outcomes(const SimCon
     int k, ev = -1;
     if (all) {
       k = it;
-    } else if (sorted_list<R, SORT>(ne)) {  // next event in the sorted list
+    } else if (sorted_list<R>(a, ne)) {  // next event in the sorted list
       if (idx >= ne || (L.skey[idx] >> 16) != ci) break;
       k = L.skey[idx] & 0xffff;
       ev = L.eord[idx];
@@ -824,7 +825,7 @@ __device__ inline void tile_draw(const SimConst& K, const PartArgs& a, int lo, i
 // caller has zeroed D[0, ns) and the record pool count before a barrier (each
 // block-wide barrier costs the whole tile its slowest wave, so none is spent
 // on that here).
-template <int SIG, class R, bool FULL, bool LANE_ONLY, bool SORT, class Lds>
+template <int SIG, class R, bool FULL, bool LANE_ONLY, class Lds>
 __device__ __attribute__((always_inline)) inline void tile_run(const SimConst& K, const PartArgs& a, int li, int call,
                                 int64_t step, int c0, int ncells, int s0, int ns, const R* v0,
                                 R* u, R* D, int* mark, int* tl, int tagbase, int st, int stu,
@@ -838,7 +839,7 @@ __device__ __attribute__((always_inline)) inline void tile_run(const SimConst& K
   unsigned long long acc = 0, gmx = 0;
   // small outcomes, one per lane, into the record pool
   if (!all) {
-    if (sorted_list<R, SORT>(ne)) {
+    if (sorted_list<R>(a, ne)) {
       // The list sorted by (cell, outcome) keys, which are distinct: each
       // event's rank, on the waves after the first (idle while the first
       // wave's lanes run the outcomes), so that the cell threads below find
@@ -880,7 +881,7 @@ __device__ __attribute__((always_inline)) inline void tile_run(const SimConst& K
     if (n < 2) continue;
     int first = 0;  // (sorted list) the cell's first event in key order
     if (!all) {  // skip cells without events quickly
-      if (sorted_list<R, SORT>(ne)) {
+      if (sorted_list<R>(a, ne)) {
         first = lower_bound_i(L.skey, ne, ci << 16);
         if (first >= ne || (L.skey[first] >> 16) != ci) continue;
       } else {
@@ -889,7 +890,7 @@ __device__ __attribute__((always_inline)) inline void tile_run(const SimConst& K
         if (!any) continue;
       }
     }
-    cell_outcomes<SIG, R, FULL, LANE_ONLY, SORT>(K, a, call, step, c, ci, cs, n, v0, u, D, mark, tl, tagbase,
+    cell_outcomes<SIG, R, FULL, LANE_ONLY>(K, a, call, step, c, ci, cs, n, v0, u, D, mark, tl, tagbase,
                                            st, stu, L, li, ne, first, all, acc, gmx);
   }
   count_pairs(a, acc, gmx);
@@ -932,7 +933,7 @@ __device__ __attribute__((always_inline)) inline void tile_collide(const SimCons
   const int64_t steps[2] = {step, step};
   tile_draw(K, a, 0, 1, calls, steps, c0, ncells, L);
   __syncthreads();
-  tile_run<SIG, R, FULL, false, true>(K, a, 0, call, step, c0, ncells, s0, ns, v0, u, D, mark, tl, tagbase, st,
+  tile_run<SIG, R, FULL, false>(K, a, 0, call, step, c0, ncells, s0, ns, v0, u, D, mark, tl, tagbase, st,
                          stu, L);
 }
 
@@ -1292,7 +1293,7 @@ __global__ void __launch_bounds__(kTileThreads, PAIRS == kPairsDrawn    ? (FAM =
             return;
           }
         }
-        tile_run<SIG, double, FULL, FAST, true>(K, a, li, call, step, c0, ncells, s0, ns, v0, u, D, mark,
+        tile_run<SIG, double, FULL, FAST>(K, a, li, call, step, c0, ncells, s0, ns, v0, u, D, mark,
                                                 tl, li ? K.navg : 0, st, NP, cl,
                                                 few_cells ? lcs : nullptr);
       }

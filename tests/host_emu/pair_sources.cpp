@@ -47,6 +47,7 @@ struct Header {
   int64_t step;
   int32_t precision, order, source, mode;  // mode: of PartArgs
   int32_t heavy_lds_n, heavy_split;
+  int32_t scan_events, unused;
 };
 
 template <class T>
@@ -250,6 +251,7 @@ int main(int argc, char** argv) {
     a.nb = h.step;
     a.na = (h.mode & kDoB) ? h.step + 1 : h.step;
     a.callB = 1;
+    a.scan_events = h.scan_events;
     const int sig = K.sigma_model == 0 ? kSigPoly : (K.omega == 1.0 ? kSigMaxwell : kSigHS);
     if (K.family == 1 && sig == kSigHS) rc = run<1, kSigHS>(K, a, h, out, x, v, ash, E);
     else if (K.family == 0 && sig == kSigPoly) rc = run<0, kSigPoly>(K, a, h, out, x, v, ash, E);

@@ -58,11 +58,13 @@ def _oracle_state(prob, disc, steps):
     return _states[at]
 
 
-def _run(harness, prob, disc, source, mode, order, precision=0, steps=1, lds_n=1920, split=1):
+def _run(harness, prob, disc, source, mode, order, precision=0, steps=1, lds_n=1920, split=1,
+         scan=0):
     from paper_2602_15130_amd import pic as P
     exe, d = harness
     blob = bytes(P.make_problem(prob)) + bytes(P.make_disc(disc))
-    blob += struct.pack("<QQqiiiiii", 5, 11, steps, precision, order, source, mode, lds_n, split)
+    blob += struct.pack("<QQqiiiiiiii", 5, 11, steps, precision, order, source, mode, lds_n, split,
+                        scan, 0)
     blob += _oracle_state(prob, disc, steps)
     (d / "in.bin").write_bytes(blob)
     r = subprocess.run([exe, str(d / "in.bin"), str(d / "out.bin")], capture_output=True, text=True,
@@ -128,6 +130,18 @@ def test_pair_sources_agree_in_every_order(harness, case, precision):
                     assert got["left"] > 0
                 if case in ("few", "many_outcomes") or (case == "chunks" and source == CHUNKS):
                     assert got["left"] == 0
+
+
+def test_scanned_event_lists_change_no_bit(harness):
+    """The mixed form's event lists (about 64 events a tile, sorted from 25 on)
+    scanned instead (PIC_SORT_EVENTS=0, which the library reads)."""
+    prob, disc = _cfg((4, 4, 4), 32, 1.0, 8)
+    ref = _run(harness, prob, disc, GENERAL, DO_B | DO_A, SHUFFLE, 1)
+    assert ref["accepted"] > 100
+    assert _same(_run(harness, prob, disc, GENERAL, DO_B | DO_A, SHUFFLE, 1, scan=1), ref)
+    from paper_2602_15130_amd import pic as P
+    with open(P.LIB_PATH, "rb") as f:
+        assert b"PIC_SORT_EVENTS" in f.read()
 
 
 # mesh, particles per cell, pairs per outcome, outcomes; workgroups per cell, LDS particles
