@@ -1000,14 +1000,14 @@ int one_step(pic_ctx* c) {
 
 // The pair counts into the counters, before the host reads those.
 int fold_counters(pic_ctx* c) {
-  k_fold_counters<<<G(c, 1), kCntSpread, 0, c->stream>>>(c->cnt, c->spread, c->flags, c->any,
-                                                         c->mstride);
+  k_fold_counters<<<G(c, 1), kCntSpread, 0, c->stream>>>(c->cnt, c->spread, c->flags, c->cgit, c->cgrr,
+                                                         c->any, c->mstride);
   LAUNCH_CHECK(c, "fold counters");
   return PIC_OK;
 }
 
-// The flags raised and, right after fold_counters (folded) or with several members,
-// the pairs above g_max, over all members; waits for the stream.  A copy to the
+// The flags raised and, right after fold_counters (folded), the pair counts over all
+// members and member 0's solver record; waits for the stream.  A copy to the
 // host is about 9 us, so one has to do: several members' are put together on
 // the device (a query of one member of 16 made 33 copies).
 int members_any(pic_ctx* c, bool folded, MembersAny& out) {
@@ -1833,27 +1833,17 @@ int pic_stats(pic_ctx* c, pic_stats_t* out) {
   if (!c || !c->ready) return PIC_ESTATE;
   if (!out) return PIC_EINVAL;
   TRY(fold_counters(c));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  int it = 0;
-  double rr = 0.0;
-  unsigned long long cnt[kCntCount];
-  HIP_TRY(c, hipMemcpy(&it, c->cgit, sizeof(it), hipMemcpyDeviceToHost));
-  HIP_TRY(c, hipMemcpy(&rr, c->cgrr, sizeof(rr), hipMemcpyDeviceToHost));
-  for (int i = 0; i < kCntCount; ++i) cnt[i] = 0;
-  for (int m = 0; m < c->members; ++m) {
-    unsigned long long cm[kCntCount];
-    HIP_TRY(c, hipMemcpy(cm, member_ptr(c, c->cnt, m), sizeof(cm), hipMemcpyDeviceToHost));
-    for (int i = 0; i < kCntCount; ++i) cnt[i] += cm[i];
-  }
+  MembersAny any;
+  TRY(members_any(c, true, any));
   out->step = c->step;
-  out->cg_iters = it;
-  out->cg_relres = rr;
-  out->n_accepted = (int64_t)cnt[kCntAccepted];
-  out->n_gmax = (int64_t)cnt[kCntGmax];
+  out->cg_iters = any.iters;
+  out->cg_relres = any.relres;
+  out->n_accepted = (int64_t)any.accepted;
+  out->n_gmax = (int64_t)any.gmax;
   out->cg_blocks = c->cg_grid;
   for (int d = 0; d < 3; ++d) out->cg_brick[d] = c->cg_q ? c->cg_bd[d] : 0;
   out->cg_members_per_launch = c->cg_members_together ? c->members : 1;
-  return check_flags(c);
+  return flags_status(c, any);
 }
 
 }  // extern "C"

@@ -159,21 +159,27 @@ __global__ void k_fill(T* p, T v, int64_t n, int64_t mstride) {
     p[i] = v;
 }
 
-// What a query of the state checks.
+// What a query of the state checks, and the counts and the solver's record that
+// it reports (one copy to the host for all of them).
 struct MembersAny {
   int flags[kFlagCount];
-  unsigned long long gmax;
+  unsigned long long gmax, accepted;
+  double relres;
+  int iters;
 };
 
 // Moves the spread counts into the counters and leaves what a query checks in
 // one place (one workgroup per member).
 __global__ void __launch_bounds__(kCntSpread) k_fold_counters(unsigned long long* cnt,
                                                               unsigned long long* spread,
-                                                              const int* flags, MembersAny* any,
+                                                              const int* flags, const int* iters,
+                                                              const double* relres, MembersAny* any,
                                                               int64_t mstride) {
   cnt = mem_z(mstride, cnt);
   spread = mem_z(mstride, spread);
   flags = mem_z(mstride, flags);
+  iters = mem_z(mstride, iters);
+  relres = mem_z(mstride, relres);
   any = mem_z(mstride, any);
   unsigned long long* c = spread + threadIdx.x * kCntStride;
   for (int i = 0; i < 2; ++i) {
@@ -183,7 +189,12 @@ __global__ void __launch_bounds__(kCntSpread) k_fold_counters(unsigned long long
   __threadfence();
   __syncthreads();
   if (threadIdx.x < kFlagCount) any->flags[threadIdx.x] = flags[threadIdx.x];
-  if (threadIdx.x == 0) any->gmax = atomicAdd(&cnt[kCntGmax], 0ull);
+  if (threadIdx.x == 0) {
+    any->gmax = atomicAdd(&cnt[kCntGmax], 0ull);
+    any->accepted = atomicAdd(&cnt[kCntAccepted], 0ull);
+    any->iters = *iters;
+    any->relres = *relres;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1417,24 +1428,29 @@ __global__ void __launch_bounds__(kBlock) k_err_velocities(SimConst K, double t,
   err_row<3>(s2, mx, part, 3, sh);
 }
 
-// What a query of the state checks, over all members of an ensemble.
+// The same over all members of an ensemble, from member 0's on; the solver's record
+// is member 0's.
 __global__ void __launch_bounds__(kBlock) k_members_any(const int* flags, const unsigned long long* cnt,
                                                         int members, int64_t mstride, MembersAny* out) {
   __shared__ int f[kFlagCount];
-  __shared__ unsigned long long g;
+  __shared__ unsigned long long g[2];
   if (threadIdx.x < kFlagCount) f[threadIdx.x] = 0;
-  if (threadIdx.x == 0) g = 0;
+  if (threadIdx.x < 2) g[threadIdx.x] = 0;
   __syncthreads();
   for (int m = threadIdx.x; m < members; m += kBlock) {
     const int* fm = (const int*)((const char*)flags + m * mstride);
     for (int i = 0; i < kFlagCount; ++i)
       if (fm[i]) atomicOr(&f[i], fm[i]);
-    const unsigned long long n = *(const unsigned long long*)((const char*)(cnt + kCntGmax) + m * mstride);
-    if (n) atomicAdd(&g, n);
+    const unsigned long long* cm = (const unsigned long long*)((const char*)cnt + m * mstride);
+    for (int i = 0; i < 2; ++i)
+      if (cm[i]) atomicAdd(&g[i], cm[i]);
   }
   __syncthreads();
   if (threadIdx.x < kFlagCount) out->flags[threadIdx.x] = f[threadIdx.x];
-  if (threadIdx.x == 0) out->gmax = g;
+  if (threadIdx.x == 0) {
+    out->accepted = g[kCntAccepted];
+    out->gmax = g[kCntGmax];
+  }
 }
 
 __global__ void __launch_bounds__(kBlock) k_err_nodes(SimConst K, double t, const double* phi,

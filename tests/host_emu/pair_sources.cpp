@@ -200,6 +200,8 @@ int main(int argc, char** argv) {
   std::vector<int> gmark(np), gtl(np), flags(kFlagCount, 0);
   std::vector<unsigned long long> counters(kCntCount, 0), spread(kCntSpread * kCntStride, 0);
   MembersAny any{};
+  const int iters = 3;
+  const double relres = 0.5;
   std::mt19937_64 rng(h.rng_seed);
   int left = 0, rc = 0;
   if (h.source == kHeavy || h.source == kSerial) {  // one FP64 collision call
@@ -260,9 +262,11 @@ int main(int argc, char** argv) {
   }
   if (rc) return rc;
   emu::run_grid(1, kCntSpread, [&] {
-    k_fold_counters(counters.data(), spread.data(), flags.data(), &any, 0);
+    k_fold_counters(counters.data(), spread.data(), flags.data(), &iters, &relres, &any, 0);
   }, h.order, rng);
-  if (any.gmax != counters[kCntGmax]) return 6;
+  if (any.gmax != counters[kCntGmax] || any.accepted != counters[kCntAccepted] || any.iters != iters ||
+      any.relres != relres)
+    return 6;
   FILE* f = std::fopen(argv[2], "wb");
   if (!f) return 1;
   wr(f, out.data(), out.size());
