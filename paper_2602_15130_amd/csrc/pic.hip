@@ -437,7 +437,7 @@ int scan_counts(pic_ctx* c) {
   ti.ncell = n;
   ti.np = (int)c->K.np;
   k_scan_local<<<G(c, nb), kBlock, 0, c->stream>>>(c->count, c->cstart, c->bsum, n, ti, c->mstride);
-  const int scanned = nb > kScanDirect;
+  const int scanned = (int64_t)nb * c->members > kScanDirect;
   if (scanned)
     k_scan_blocks<<<G(c, 1), kBlock, 0, c->stream>>>(c->bsum, nb, c->cstart, n, c->mstride);
   k_scan_add<<<G(c, nb), kBlock, 0, c->stream>>>(c->cstart, c->bsum, scanned, n, c->count, ti,

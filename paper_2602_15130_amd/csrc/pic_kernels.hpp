@@ -263,15 +263,17 @@ __global__ void __launch_bounds__(kBlock) k_count(const int* key, int* slot, int
 }
 
 // Exclusive scan of n ints, 1024 items per block: the blocks by themselves, then
-// the sum of the blocks before each.  Up to kScanDirect blocks every workgroup
-// of the second pass adds those up itself; the number of these loads grows with
-// the square, so beyond that one workgroup scans the block sums in between.
-// Second pass alone against both launches, by blocks: 5 and 10 us (256), 15 and
-// 29 (4,000), 31 and 54 (7,800); by that growth about equal at 16,384, where both
-// launches take 107.
+// the sum of the blocks before each.  Every workgroup of the second pass adds
+// those up itself, or, beyond kScanDirect blocks of all members, one workgroup
+// per member scans the block sums in between: the loads of the first form
+// grow with the members and the square of the blocks, the second's chain with the
+// blocks, its members side by side.  The first form against the second (us a sort),
+// by members x blocks: 1 x 256 -2, 1 x 4,000 -16, 1 x 16,384 -37; 4 x 4,000 -10,
+// 4 x 7,813 +10, 8 x 2,048 -9, 8 x 4,000 +27, 16 x 977 -5, 16 x 2,048 +14, 32 x 256 -5,
+// 32 x 977 +12.
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kBlock * kScanItems;
-constexpr int kScanDirect = 8192;
+constexpr int kScanDirect = 16384;
 
 // Tile tables of the sort, filled before the last pass writes their bounds.
 struct TileInit {
