@@ -272,6 +272,7 @@ struct pic_ctx {
   float* Df{};
   bool fused = true;
   bool lean_pass = true;        // lean pass instance first, general one for the tiles it defers
+  bool general_only = false;    // the general instance alone, over all tiles
   bool scan_events = false;     // mixed event lists are scanned, never sorted
   // Captured steps (pic_use_graphs): two steps per graph, one graph per
   // double-buffer parity, recorded on a private stream and replayed on the
@@ -804,8 +805,8 @@ PassFns select_pass(const SimConst& K) {
 constexpr int kDeferGrid = 2048;
 
 // Fused pass: the drawn-pairs instance (lean_pass) or the chunks instance over
-// all tiles, then the general one over the tiles it left; or the full instance
-// alone, for logged runs.
+// all tiles, then the general one over the tiles it left; or the general (general_only)
+// or, for logged runs, the full instance alone.
 int launch_particles(pic_ctx* c, const PartArgs& a0) {
   const SimConst& K = c->K;
   PartArgs a = a0;
@@ -829,11 +830,13 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
   // samplers are compiled only into the full instances
   const bool full = K.anglog != nullptr || a.pairlog != nullptr || K.chi_model != PIC_CHI_ISO ||
                     K.coding_error != 0;
-  const int first = c->lean_pass ? 2 : 3, last = full ? 0 : 1;
+  const bool coll = K.collisions || (a.mode & kCollideOnly);
+  const int first = c->lean_pass || !coll ? 2 : 3, last = full ? 0 : 1;
+  const bool alone = full || (coll && c->general_only);
   PartArgs ag = a;
-  ag.defer_list = full ? 0 : 1;
-  const dim3 grid_last = G(c, full ? tiles : std::min(tiles, kDeferGrid));
-  if (!full && first == 2 && (K.collisions || (a.mode & kCollideOnly))) {
+  ag.defer_list = alone ? 0 : 1;
+  const dim3 grid_last = G(c, alone ? tiles : std::min(tiles, kDeferGrid));
+  if (!alone && first == 2 && coll) {
     const bool by_tile =
         draw_by_tile((int64_t)tiles * c->members, (int64_t)K.nn * ((K.navg + 3) / 4) / tiles);
     const int per = draw_tiles_per_wave((int64_t)tiles * c->members);
@@ -847,7 +850,7 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
     LAUNCH_CHECK(c, "draw pairs");
     c->defer_empty = true;
   }
-  if (!full) {  // an empty list of deferred tiles
+  if (!alone) {  // an empty list of deferred tiles
     if (!c->defer_empty) TRY(fill(c, c->defer, 0, 1));
     c->defer_empty = false;
   }
@@ -864,7 +867,7 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
       fm = fns.mixed_dev;
     }
     const int s = c->cur;
-    if (!full) {
+    if (!alone) {
       fm[first]<<<G(c, tiles), dim3(kTileThreads), 0, c->stream>>>(K, M, a, c->off[s], c->vf[s],
                                                               c->asf[s], c->E32);
       LAUNCH_CHECK(c, "particles (mixed, lean)");
@@ -874,7 +877,7 @@ int launch_particles(pic_ctx* c, const PartArgs& a0) {
     LAUNCH_CHECK(c, "particles (mixed)");
     return PIC_OK;
   }
-  if (!full) {
+  if (!alone) {
     fns.f64[first]<<<G(c, tiles), kTileThreads, 0, c->stream>>>(K, a);
     LAUNCH_CHECK(c, "particles (lean)");
   }
@@ -1245,8 +1248,25 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     // mixed and 28.7 / 40.5 FP64, 0.36 pairs 33.8 / 38.7 mixed.
     // PIC_LEAN_PASS=0/1 overrides.
     const double need = pairs * (double)c->K.navg * ((double)kTileB / std::max(nbar, 1.0));
-    c->lean_pass = !c->K.collisions || need <= 0.5 * kRecCap;
-    if (const char* lp = std::getenv("PIC_LEAN_PASS")) c->lean_pass = lp[0] == '1';
+    c->lean_pass = need <= 0.5 * kRecCap;
+    // The chunks leave a tile beyond its LDS slots, or with an outcome of more than
+    // kDenseMaxPairs pairs, to the general instance, whose chain over the outcomes is
+    // as long for one tile as for all of them, and the chunks before it are then
+    // time on top: it runs alone where the mean cell alone is as large as the slots
+    // beyond a tile's start, or where the densest cells are expected beyond those
+    // pairs (the density's peak, 3.5 standard deviations up).  Steps of two members,
+    // chunks first against the general instance alone (ms; FP64): 16^3, 32 a cell,
+    // 16 outcomes: 1.5 / 3.2 at 12 pairs an outcome, 2.4 / 4.3 at 16, 15.2 / 8.4 at 30;
+    // 24^3, 20 a cell, 8 outcomes: 2.3 / 3.1 at 12, 6.3 / 3.8 at 16, 13.9 / 6.7 at 30; 12^3,
+    // 60 a cell, 8 outcomes, 10 pairs: 1.19 / 1.21; 8^3, 120 a cell: 1.25 / 1.04.
+    const double peak = prob->family == PIC_MMS_CFG ? 1.0 + std::fabs(prob->rho_amp) : 2.7;
+    const double most = peak * nbar + 3.5 * std::sqrt(peak * nbar);
+    c->general_only = !c->lean_pass && (nbar > kLdsSlots - kTileB ||
+                                        most * (most - 1.0) * c->K.pmax / 2.0 > (double)kDenseMaxPairs);
+    if (const char* lp = std::getenv("PIC_LEAN_PASS")) {
+      c->lean_pass = lp[0] == '1';
+      c->general_only = false;
+    }
     // PIC_SORT_EVENTS=0: the mixed form's event lists (the full and the general
     // instance) are scanned however long they are.
     if (const char* se = std::getenv("PIC_SORT_EVENTS")) c->scan_events = se[0] != '1';

@@ -16,7 +16,7 @@
 // the tile draws them in chunks (tile_dense); each slot's thread then adds up the
 // changes of its own slot in outcome order.  The full and general instances
 // (logs, anisotropic scattering, tiles beyond the LDS slots, outcomes of more than
-// 64 pairs) run event lists instead: (1) one lane per (cell, outcome) draws N_pairs
+// kDenseMaxPairs pairs) run event lists instead: (1) one lane per (cell, outcome) draws N_pairs
 // (Algorithm 1) and records the few lanes that have candidate pairs; (2) one
 // lane per such outcome with at most kSmallPairs pairs runs it on a private
 // list of the velocities it changes and stores the changes; (3) one thread per
@@ -92,7 +92,11 @@ struct CellRanges {
 };
 // LDS of a call that draws and applies its pairs in chunks (tile_dense).
 constexpr int kDenseChunk = 256;   // pairs of a chunk, one per thread
-constexpr int kDenseMaxPairs = 64; // pairs of an outcome at most
+// Pairs of an outcome at most.  (One thread runs an outcome, and looks every pair's
+// particles up among those changed so far; two-member steps as at general_only's
+// rule, with at most 64 / 96 / 128: 20 pairs an outcome at 16^3 8.6 / 3.7 / 3.6 ms, 40 pairs,
+// where most tiles hold more than any of these, 16.5 / 22 / 25.)
+constexpr int kDenseMaxPairs = 96;
 static_assert(kDenseChunk == kTileThreads, "a thread per pair of a chunk");
 template <class R>
 struct DenseLds {

@@ -103,7 +103,7 @@ CASES = {"few": _cfg((4, 4, 4), 32, 0.06, 16),
          "over_four": _cfg((4, 4, 4), 40, 4.2, 3),   # outcomes of more pairs than a list takes
          "overflow": _cfg((4, 3, 4), 32, 0.9, 20),   # lists that overflow
          "chunks": _cfg((3, 4, 3), 30, 2.0, 70),     # several chunks and blocks of items
-         "over_64": _cfg((3, 3, 3), 110, 66.0, 2),   # outcomes over a chunk's most pairs
+         "over_96": _cfg((3, 3, 3), 110, 90.0, 2),   # outcomes over a chunk's most pairs
          "large_cells": _cfg((3, 3, 3), 350, 0.5, 3),
          "paper": _paper(4)}
 
@@ -126,7 +126,7 @@ def test_pair_sources_agree_in_every_order(harness, case, precision):
             for source in (DRAWN, DRAWN_BY_TILE, CHUNKS):
                 got = _run(harness, prob, disc, source, mode, order, precision)
                 assert _same(got, ref), (mode, order, source)
-                if case in ("large_cells", "over_64") or (case == "overflow" and source != CHUNKS):
+                if case in ("large_cells", "over_96") or (case == "overflow" and source != CHUNKS):
                     assert got["left"] > 0
                 if case in ("few", "many_outcomes") or (case == "chunks" and source == CHUNKS):
                     assert got["left"] == 0
