@@ -107,12 +107,6 @@ static int run(const SimConst& K, PartArgs a, const Header& h, std::vector<doubl
   const int nn = K.nn;
   std::mt19937_64 rng(h.rng_seed);
   if (h.precision == 0) {
-    std::vector<double> drift(3 * np);
-    if (FAM == 0 && (a.mode & kDoA)) {
-      a.mdrift = drift.data();
-      run_grid2((unsigned)((np + kBlock - 1) / kBlock), 1, kBlock,
-                [&] { k_paper_drift_f64(K, a, drift.data()); }, h.order, rng);
-    }
     run_pass<double, FAM, SIG>(K, a, h, rng, [&](int which, const PartArgs& args) {
       if (which == 0) k_particles_f64<FAM, SIG, false, false>(K, args);
       else if (which == 1) k_particles_f64<FAM, SIG, false, true, kPairsDrawn>(K, args);
@@ -124,7 +118,7 @@ static int run(const SimConst& K, PartArgs a, const Header& h, std::vector<doubl
     }
     return 0;
   }
-  std::vector<float> off(3 * np), vf(3 * np), ashf(3 * np), E32(3 * (size_t)nn), drift(3 * np);
+  std::vector<float> off(3 * np), vf(3 * np), ashf(3 * np), E32(3 * (size_t)nn);
   for (int64_t i = 0; i < np; ++i) {
     const double xp[3] = {x[i], x[np + i], x[2 * np + i]};
     int c[3];
@@ -138,11 +132,6 @@ static int run(const SimConst& K, PartArgs a, const Header& h, std::vector<doubl
   }
   for (int n = 0; n < nn; ++n)
     for (int d = 0; d < 3; ++d) E32[3 * n + d] = (float)E[(size_t)d * nn + n];
-  if (FAM == 0 && (a.mode & kDoA)) {
-    a.mdrift32 = drift.data();
-    run_grid2((unsigned)((np + kBlock - 1) / kBlock), 1, kBlock,
-              [&] { k_paper_drift_mixed(K, a, off.data(), drift.data()); }, h.order, rng);
-  }
   const MixConst M = mix_const(K, a);
   run_pass<float, FAM, SIG>(K, a, h, rng, [&](int which, const PartArgs& args) {
     auto go = [&](auto fn) { fn(K, M, args, off.data(), vf.data(), ashf.data(), E32.data()); };
@@ -255,9 +244,7 @@ int main(int argc, char** argv) {
     a.callB = 1;
     a.scan_events = h.scan_events;
     const int sig = K.sigma_model == 0 ? kSigPoly : (K.omega == 1.0 ? kSigMaxwell : kSigHS);
-    if (K.family == 1 && sig == kSigHS) rc = run<1, kSigHS>(K, a, h, out, x, v, ash, E);
-    else if (K.family == 0 && sig == kSigPoly) rc = run<0, kSigPoly>(K, a, h, out, x, v, ash, E);
-    else rc = 4;
+    rc = K.family == 1 && sig == kSigHS ? run<1, kSigHS>(K, a, h, out, x, v, ash, E) : 4;
     left = h.source == kGeneral ? 0 : defer[0];
   }
   if (rc) return rc;
