@@ -450,7 +450,7 @@ int scan_counts(pic_ctx* c) {
 }
 
 // The particles bucketed by cell (keys, slots and counts already computed): the
-// source index and the cell of every slot.
+// source index of every slot.
 int bucket_particles(pic_ctx* c) {
   TRY(scan_counts(c));
   int np = (int)c->K.np;

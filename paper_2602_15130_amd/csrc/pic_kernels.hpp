@@ -32,7 +32,9 @@ constexpr int kLdsSlots = PIC_LDS_SLOTS;          // LDS-resident slots per tile
 #ifndef PIC_F64_WAVES
 #define PIC_F64_WAVES 4  // also the LDS limit: four 33 KB tiles per CU
 #endif
-// The same for the lean instances (smaller: no general collision path).
+// The same for the lean instances with event lists in the tile (no general
+// collision path).  The library launches the two forms below in their place; this
+// one is the event lists' reference in the emulated tests.
 #ifndef PIC_MIXED_LEAN_WAVES
 #define PIC_MIXED_LEAN_WAVES 6
 #endif

@@ -12,9 +12,9 @@
 // LDS when they fit and in global scratch otherwise.
 //
 // Collisions in a tile: where the pairs are few they were drawn before the pass
-// (k_draw_pairs) and one thread per outcome applies them; where they are many
-// the tile draws them in chunks (tile_dense); each slot's thread then adds up the
-// changes of its own slot in outcome order.  The full and general instances
+// (k_draw_pairs, k_draw_tile) and one thread per outcome applies them; where they
+// are many the tile draws them in chunks (tile_dense); each slot's thread then adds
+// up the changes of its own slot in outcome order.  The full and general instances
 // (logs, anisotropic scattering, tiles beyond the LDS slots, outcomes of more than
 // kDenseMaxPairs pairs) run event lists instead: (1) one lane per (cell, outcome) draws N_pairs
 // (Algorithm 1) and records the few lanes that have candidate pairs; (2) one
@@ -133,9 +133,9 @@ struct PartArgs {
   unsigned long long* counters;
   unsigned long long* spread;  // the pair counts by workgroup (null: in counters themselves)
   int* flags;
-  // tiles the lean instance leaves to the general one: [0] count, [1] workgroups
-  // done with the list, [2 ..] tile indices; the general instance works through
-  // the list when defer_list is set, else through all tiles
+  // tiles the first instance leaves to the general one: [0] count, [1 ..] tile
+  // indices; the general instance works through the list when defer_list is set,
+  // else through all tiles
   int* defer;
   int ntiles, defer_list;
   int scan_events;  // the mixed form's event lists are never sorted
