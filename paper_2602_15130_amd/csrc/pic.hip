@@ -1243,9 +1243,10 @@ int create(pic_ctx** out, const pic_problem* prob, const pic_discretization* dis
     // kRecCap pairs per call of a tile; expected are N_pairs-mean N_avg (cells
     // per tile).  Above half the list (the paper's densest cells have 1.7 times
     // the mean's pairs per tile) the instance that draws its pairs in chunks in
-    // the tile runs instead.  Runs with the lists against chunks (ms; 64^3,
-    // initialisation and norms included): 0.06 pairs per outcome 19.7 / 27.8
-    // mixed and 28.7 / 40.5 FP64, 0.36 pairs 33.8 / 38.7 mixed.
+    // the tile runs instead.  Steps with the lists against chunks (us; 64^3, 32 a
+    // cell, 16 outcomes, by pairs expected in a tile's list; mixed, FP64): 726 / 1,144 and
+    // 1,229 / 1,858 at 16, 847 / 1,240 and 1,469 / 1,977 at 64, 1,144 / 1,318 and
+    // 2,379 / 2,079 at 96; 32^3: 199 / 245 and 264 / 335 at 64, 258 / 252 and 475 / 343 at 80.
     // PIC_LEAN_PASS=0/1 overrides.
     const double need = pairs * (double)c->K.navg * ((double)kTileB / std::max(nbar, 1.0));
     c->lean_pass = need <= 0.5 * kRecCap;
